@@ -226,8 +226,11 @@ typedef struct psf_config {
                                 triple per cell.  PSF_PAYLOAD_SH2_YCOCG:
                                 luminance as two spherical-harmonic bands
                                 over the normal plus YCoCg chroma (below);
-                                F32 state and the direct insert strategy
-                                only (NOT_SUPPORTED otherwise). */
+                                F32 state only, and insert_mode AUTO (the
+                                records are binned and summed a partition
+                                at a time, with 40 bytes of staging per
+                                record of max_batch) or DIRECT
+                                (NOT_SUPPORTED otherwise). */
 } psf_config;
 
 /* Cell payloads.  SH2_YCOCG (Sec. 2.6: normal variation within a cell as

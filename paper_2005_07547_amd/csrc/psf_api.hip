@@ -169,13 +169,18 @@ bool validate(const psf_config* c, std::string* why) {
 
 struct Layout {
   size_t sh = 0, sh_acc = 0, var = 0, acc_q = 0;
-  size_t stats = 0, touch = 0, slots = 0, keys = 0, acc = 0, stage_key = 0, stage_v = 0, stage_q = 0, runs = 0,
-         runs_t = 0, perm = 0, total = 0;
+  size_t stats = 0, touch = 0, slots = 0, keys = 0, acc = 0, stage_key = 0, stage_v = 0, stage_q = 0,
+         stage_n = 0, runs = 0, runs_t = 0, perm = 0, total = 0;
   uint32_t part_log2 = 0;
   bool part = false;
   uint64_t cap = 0;
   uint32_t tiles = 0;
 };
+
+// Records per binning thread (the SH payload's binning pass has one width).
+uint32_t bin_per_of(const psf_config& c) {
+  return c.bin_per && c.payload == PSF_PAYLOAD_RGB ? c.bin_per : kDefaultBinPer;
+}
 
 Layout layout_of(const psf_config& c) {
   Layout L;
@@ -192,7 +197,8 @@ Layout layout_of(const psf_config& c) {
   L.part_log2 = c.part_log2 ? c.part_log2 : def;
   if (L.part_log2 > c.log2_slots) L.part_log2 = c.log2_slots;
   const uint64_t P = 1ull << (c.log2_slots - L.part_log2);
-  L.part = c.insert_mode != PSF_INSERT_DIRECT && P <= kMaxPartitions && c.payload == PSF_PAYLOAD_RGB;
+  L.part = c.insert_mode != PSF_INSERT_DIRECT && P <= kMaxPartitions;
+  const bool sh = c.payload == PSF_PAYLOAD_SH2_YCOCG;
   size_t off = 0;
   L.stats = off;
   off = align_up(off + sizeof(psf::DevStats), 256);
@@ -222,7 +228,7 @@ Layout layout_of(const psf_config& c) {
     }
   }
   if (L.part) {
-    const uint64_t tile = psf::bin_tile(c.bin_per ? c.bin_per : kDefaultBinPer);
+    const uint64_t tile = psf::bin_tile(bin_per_of(c));
     L.cap = c.max_batch ? c.max_batch : kDefaultBatch;
     L.tiles = (uint32_t)((L.cap + tile - 1) / tile);
     L.cap = (uint64_t)L.tiles * tile;
@@ -234,12 +240,18 @@ Layout layout_of(const psf_config& c) {
       L.stage_q = off;
       off = align_up(off + L.cap * 4, 256);
     }
+    if (sh) {
+      L.stage_n = off;
+      off = align_up(off + L.cap * 16, 256);
+    }
     L.runs = off;
     off = align_up(off + (P + 1) * (uint64_t)L.tiles * 4, 256);
     L.runs_t = off;  // rows padded to a multiple of 4 tiles (16-byte loads)
     off = align_up(off + (P + 1) * (uint64_t)((L.tiles + 3) & ~3u) * 4, 256);
-    L.perm = off;
-    off = align_up(off + L.cap * 2, 256);
+    if (!sh) {
+      L.perm = off;
+      off = align_up(off + L.cap * 2, 256);
+    }
   }
   L.total = off;
   return L;
@@ -297,10 +309,7 @@ bool transpose_runs(const psf_table* t, uint32_t ntiles) {
 
 psf_status do_insert(psf_table* t, const psf::RecPtrs& rp, uint64_t n, hipStream_t s) {
   hipError_t e;
-  if (t->tv.sh) {
-    e = timed(t, PSF_K_INSERT_DIRECT, s, [&] { return psf::launch_insert_sh(rp, n, t->kp, t->tv, s); });
-    if (e != hipSuccess) return hip_fail(e, "insert launch");
-  } else if (t->partitioned) {
+  if (t->partitioned) {
     for (uint64_t off = 0; off < n; off += t->pv.capacity) {
       const uint64_t m = (n - off < t->pv.capacity) ? n - off : t->pv.capacity;
       const psf::RecPtrs sub = offset_rec(rp, off);
@@ -313,12 +322,17 @@ psf_status do_insert(psf_table* t, const psf::RecPtrs& rp, uint64_t n, hipStream
       if (e == hipSuccess && pv.runs_t)
         e = timed(t, PSF_K_TRANSPOSE, s, [&] { return psf::launch_transpose_runs(t->tv, pv, nt, s); });
       if (e == hipSuccess)
-        e = timed(t, PSF_K_MERGE, s, [&] { return psf::launch_merge(m, t->tv, pv, nullptr, false, s); });
+        e = timed(t, PSF_K_MERGE, s, [&] {
+          return t->tv.sh ? psf::launch_merge_sh(m, t->tv, pv, nullptr, s)
+                          : psf::launch_merge(m, t->tv, pv, nullptr, false, s);
+        });
       if (e != hipSuccess) return hip_fail(e, "partitioned insert launch");
     }
   } else {
-    e = timed(t, PSF_K_INSERT_DIRECT, s,
-              [&] { return psf::launch_insert_direct(rp, n, t->kp, t->tv, s); });
+    e = timed(t, PSF_K_INSERT_DIRECT, s, [&] {
+      return t->tv.sh ? psf::launch_insert_sh(rp, n, t->kp, t->tv, s)
+                      : psf::launch_insert_direct(rp, n, t->kp, t->tv, s);
+    });
     if (e != hipSuccess) return hip_fail(e, "insert launch");
   }
   t->pending = true;
@@ -426,11 +440,12 @@ PSF_API psf_status psf_create_table(const psf_config* cfg, void* device_buffer, 
     t->pv.stage_key = reinterpret_cast<unsigned long long*>(b + L.stage_key);
     t->pv.stage_v = reinterpret_cast<float4*>(b + L.stage_v);
     t->pv.stage_q = L.stage_q ? reinterpret_cast<float*>(b + L.stage_q) : nullptr;
+    t->pv.stage_n = L.stage_n ? reinterpret_cast<float4*>(b + L.stage_n) : nullptr;
     t->pv.weights = 0;
     t->pv.runs = reinterpret_cast<uint32_t*>(b + L.runs);
     t->pv.runs_t = reinterpret_cast<uint32_t*>(b + L.runs_t);
-    t->pv.perm = reinterpret_cast<uint16_t*>(b + L.perm);
-    t->pv.tile = psf::bin_tile(cfg->bin_per ? cfg->bin_per : kDefaultBinPer);
+    t->pv.perm = L.perm ? reinterpret_cast<uint16_t*>(b + L.perm) : nullptr;
+    t->pv.tile = psf::bin_tile(bin_per_of(*cfg));
     t->pv.max_tiles = L.tiles;
     t->pv.capacity = L.cap;
     t->partitioned = true;
@@ -522,7 +537,7 @@ PSF_API psf_status psf_iterate(psf_table* t, const psf_records* rec, uint64_t n,
     // when the queries are the records being inserted, the merge pass hands
     // every staged entry its cell's new value and the unstage pass returns
     // them in record order: no second lookup
-    const bool fq = nq == n && same_vertices(rec, q);
+    const bool fq = nq == n && !t->tv.sh && same_vertices(rec, q);
     psf::PartView pv = t->pv;
     if (!fq) pv.perm = nullptr;
     pv.weights = rp.weight != nullptr;
@@ -532,7 +547,10 @@ PSF_API psf_status psf_iterate(psf_table* t, const psf_records* rec, uint64_t n,
     if (e == hipSuccess && pv.runs_t)
       e = timed(t, PSF_K_TRANSPOSE, s, [&] { return psf::launch_transpose_runs(t->tv, pv, nt, s); });
     if (e == hipSuccess)
-      e = timed(t, PSF_K_MERGE_BLEND, s, [&] { return psf::launch_merge(n, t->tv, pv, &t->bp, fq, s); });
+      e = timed(t, PSF_K_MERGE_BLEND, s, [&] {
+        return t->tv.sh ? psf::launch_merge_sh(n, t->tv, pv, &t->bp, s)
+                        : psf::launch_merge(n, t->tv, pv, &t->bp, fq, s);
+      });
     if (e != hipSuccess) return hip_fail(e, "fused insert launch");
     t->submitted += n;
     t->updates++;
@@ -959,7 +977,7 @@ PSF_API psf_status psf_iterate_batch(psf_batch* b, const psf_session* sessions, 
   // rather than slowing every other session's merge blocks.
   auto candidate = [&](const psf_session& ss) {
     const psf_table* t = ss.table;
-    return ss.n > 0 && t->partitioned && !t->pending && ss.n <= t->pv.capacity;
+    return ss.n > 0 && t->partitioned && !t->tv.sh && !t->pending && ss.n <= t->pv.capacity;
   };
   uint32_t part_cap = 0;
   for (uint32_t i = 0; i < k; ++i)

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "psf.h"
 #include "psf_device.h"
 
@@ -29,6 +31,8 @@ struct PartView {
                                   // each entry's answer {r, g, b, 0} over it.
   float* stage_q;                 // per staged entry, the sum of its records' squared
                                   // luminances (tables that keep the variance; else null)
+  float4* stage_n;                // per staged entry, its record's normal (SH payload
+                                  // tables; else null)
   uint32_t weights;               // this launch's records carry weights (n is then a
                                   // weight, one record per entry)
   uint32_t* runs;                 // [tile][partition + 1]: exclusive offsets in the tile
@@ -42,6 +46,34 @@ struct PartView {
   uint32_t max_tiles;             // tiles per launch
   uint64_t capacity;              // records per launch
 };
+
+// Raise a kernel's dynamic-LDS limit only as far as the launch needs (and
+// only when it exceeds the default 64 KiB).  The limit belongs to the
+// function on the current device; the largest value set is remembered per
+// device (devices past the table are set on every launch).
+constexpr int kLdsDevices = 64;
+struct LdsLimit {
+  std::atomic<int> bytes[kLdsDevices];
+};
+
+inline hipError_t lds_limit(const void* fn, size_t bytes, LdsLimit* cur) {
+  if (bytes <= 65536) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool known = dev >= 0 && dev < kLdsDevices;
+  if (known && (int)bytes <= cur->bytes[dev].load(std::memory_order_relaxed)) return hipSuccess;
+  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess && known) {
+    int prev = cur->bytes[dev].load(std::memory_order_relaxed);
+    while ((int)bytes > prev && !cur->bytes[dev].compare_exchange_weak(prev, (int)bytes)) {
+    }
+  }
+  return e;
+}
+
+// What a partitioned launch of n records needs of its table and staging.
+bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n);
 
 hipError_t launch_keys(const RecPtrs& rec, uint64_t n, const KeyParams& kp, unsigned long long* out,
                        hipStream_t s);
@@ -156,6 +188,10 @@ hipError_t launch_philox(const uint32_t* ctr, const uint32_t* key, uint64_t n, u
 // streaming fit + blend, lookup evaluating the luminance at the normal.
 hipError_t launch_insert_sh(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const TableView& tv,
                             hipStream_t s);
+// Partitioned insert of an SH payload table's binned records (launch_bin
+// staged their normals); fuse != nullptr fits and blends the frame in the
+// same pass (no pending samples).
+hipError_t launch_merge_sh(uint64_t n, const TableView& tv, const PartView& pv, const BlendParams* fuse, hipStream_t s);
 hipError_t launch_update_sh(const TableView& tv, const BlendParams& bp, uint64_t nslots, hipStream_t s);
 hipError_t launch_query_sh(const QryPtrs& q, uint64_t n, const KeyParams& kp, const TableView& tv, float* out,
                            uint8_t* found, hipStream_t s);

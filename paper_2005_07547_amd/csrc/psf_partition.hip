@@ -32,10 +32,9 @@
 //
 // A partition is owned by exactly one block in the merge pass, so the
 // write-back uses plain loads and stores.
-#include <atomic>
-
 #include "psf_device.h"
 #include "psf_internal.h"
+#include "psf_runs.h"
 
 namespace psf {
 
@@ -111,8 +110,11 @@ __device__ uint32_t block_exclusive_scan(uint32_t* cnt, uint32_t m, uint32_t* s_
 // level rule) and kXWeight (MIS weights: every sample is its own entry with
 // value w (r, g, b) and n = w; a weight is read only after the sort, which
 // also counts the samples it rejects); separate instantiations keep the
-// extra loads and their registers out of the common case.
-constexpr uint32_t kXFootprint = 1, kXWeight = 2;
+// extra loads and their registers out of the common case.  kXNormal: a table
+// with the SH payload, whose sums need every sample's normal: each sample is
+// its own entry and its normal, read again after the sort, is staged beside
+// the value.
+constexpr uint32_t kXFootprint = 1, kXWeight = 2, kXNormal = 4;
 
 __device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v, uint32_t d) {
   const uint32_t lo = (uint32_t)__shfl_up((int)(uint32_t)v, d);
@@ -138,7 +140,7 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
 template <uint32_t kPer, uint32_t kX>
 __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const KeyParams& kp,
                                          const TableView& tv, const PartView& pv, uint32_t tile) {
-  constexpr bool kFp = (kX & kXFootprint) != 0, kW = (kX & kXWeight) != 0;
+  constexpr bool kFp = (kX & kXFootprint) != 0, kW = (kX & kXWeight) != 0, kN = (kX & kXNormal) != 0;
   extern __shared__ uint32_t s_dyn_bin[];
   __shared__ uint32_t s_wave[kBinThreads / 64 + 1];
   __shared__ unsigned long long s_cont[kBinThreads / 64][kPer];  // per wave and record row: run continuations
@@ -153,7 +155,7 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   // entries of their own)
   const bool var = tv.var != nullptr;
   constexpr bool kQRuns = kPer <= 8;
-  const bool premerge = !kW && (kQRuns || !var);
+  const bool premerge = !kW && !kN && (kQRuns || !var);
   for (uint32_t p = tid; p <= P; p += kBinThreads) s_hist[p] = 0;
   __syncthreads();
 
@@ -357,6 +359,14 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
       pv.stage_q[t0 + (pos[j] & kPosBits)] = q;
     }
   }
+  if (kN) {
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+      if (!own_entry(j)) continue;
+      const uint64_t i = t0 + (uint64_t)j * kBinThreads + tid;
+      pv.stage_n[t0 + (pos[j] & kPosBits)] = make_float4(rec.nx[i], rec.ny[i], rec.nz[i], 0.0f);
+    }
+  }
   float wn[kW ? kPer : 1];
   if (kW) {
     // The weights are first read here.  A sample whose weight is not finite
@@ -371,9 +381,11 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
       const float w = rec.weight[t0 + (uint64_t)j * kBinThreads + tid];
       if (pos[j] & kPosLookupOnly) continue;
       if (__builtin_isfinite(w) && w > 0.0f) {
-        rgb[j][0] *= w;
-        rgb[j][1] *= w;
-        rgb[j][2] *= w;
+        if (!kN) {  // (the SH sums weight the sample themselves, in binary64)
+          rgb[j][0] *= w;
+          rgb[j][1] *= w;
+          rgb[j][2] *= w;
+        }
         wn[j] = w;
       } else {
         ++n_skip;
@@ -453,32 +465,10 @@ __global__ void __launch_bounds__(kTransposeThreads) k_transpose_runs(PartView p
 }
 
 // ------------------------------------------------------------------ merge
-// Blocks are dispatched to the 8 XCDs round-robin; give each XCD a
-// contiguous range of partitions so the offset rows they share stay in one
-// L2.
-__device__ __forceinline__ uint32_t xcd_partition(uint32_t b, uint32_t P) {
-  if (P < 8 || (P & 7u)) return b;
-  return (b & 7u) * (P >> 3) + (b >> 3);
-}
-
-constexpr uint32_t kRunsPerLane = 4;  // consecutive tile runs each lane keeps in registers
-constexpr uint32_t kEntryBatch = 4;  // entries per lane loaded before processing
 // Batches per wave whose (entry, slot) pairs stay in registers for the
 // fused query; a wave with more batches finds the later entries' slots again.
 constexpr uint32_t kKeepBatches = 2;
 constexpr uint32_t kLookupLater = 0xfffffffeu;  // kept slot of a lookup-only entry
-
-// Largest lane l with excl[l] <= e, where excl is a non-decreasing per-lane
-// value (all lanes of the wave must call this).
-__device__ __forceinline__ uint32_t wave_upper_bound(uint32_t excl, uint32_t e) {
-  uint32_t a = 0;
-#pragma unroll
-  for (uint32_t step = 32; step > 0; step >>= 1) {
-    const uint32_t v = (uint32_t)__shfl((int)excl, (int)(a + step));
-    if (a + step < 64 && v <= e) a += step;
-  }
-  return a;
-}
 
 // One partition: blk is the block's index among the partition blocks of this
 // table (the XCD-aware order maps it to a partition).  With results (fused
@@ -500,7 +490,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   extern __shared__ unsigned long long s_dyn[];
   __shared__ uint32_t s_dropped, s_nlist, s_sat;
   __shared__ uint32_t s_hist[16];
-  const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = __lane_id();
   constexpr uint32_t kWaves = kThreads / 64;
   const uint32_t P = 1u << (tv.log2_slots - tv.part_log2);
   const uint32_t B = 1u << tv.part_log2;
@@ -517,123 +507,9 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   const bool var = tv.var != nullptr;
   // the touched slots' indices (B entries), after the sums
   uint16_t* s_list = reinterpret_cast<uint16_t*>(s_sumx + ((var || wtd) ? B : 0u));
-  const uint32_t tile = pv.tile;
   if (!kFused) results = false;
 
-  // Each wave owns a contiguous slice of the tiles; it keeps up to
-  // 64 * kRunsPerLane of this partition's runs (offsets) in registers.
-  // (a multiple of 4 tiles, so that a lane's runs are one 16-byte load)
-  const uint32_t per_wave = ((ntiles + kWaves - 1) / kWaves + 3u) & ~3u;
-  const uint32_t w_lo = wave * per_wave;
-  const uint32_t w_hi = (w_lo + per_wave < ntiles) ? w_lo + per_wave : ntiles;
-  uint32_t r_lo[kRunsPerLane], r_hi[kRunsPerLane];
-  uint32_t loaded = ~0u;  // chunk of runs held in registers
-  const uint32_t stride = (pv.max_tiles + 3u) & ~3u;
-  const uint32_t* row_lo = pv.runs_t + (uint64_t)p * stride;
-  const uint32_t* row_hi = row_lo + stride;
-  auto load_runs = [&](uint32_t c0) {
-    const uint32_t t = c0 + lane * kRunsPerLane;  // a multiple of 4
-    if (pv.runs_t) {
-      // transposed table: two 16-byte loads (t + 3 < stride: inside the row)
-      uint4 lo = make_uint4(0, 0, 0, 0), hi = make_uint4(0, 0, 0, 0);
-      if (t < w_hi) {
-        lo = *reinterpret_cast<const uint4*>(row_lo + t);
-        hi = *reinterpret_cast<const uint4*>(row_hi + t);
-      }
-      const uint32_t l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-      for (uint32_t j = 0; j < kRunsPerLane; ++j) {
-        const bool in = t + j < w_hi;
-        r_lo[j] = in ? l4[j] : 0u;
-        r_hi[j] = in ? h4[j] : 0u;
-      }
-    } else {
-      // the bin pass's table: one column, read in place (the lines are
-      // shared by the neighbouring partitions an XCD runs at the same time)
-#pragma unroll
-      for (uint32_t j = 0; j < kRunsPerLane; ++j) {
-        r_lo[j] = 0;
-        r_hi[j] = 0;
-        if (t + j < w_hi) {
-          const uint32_t* offs = pv.runs + (uint64_t)(t + j) * (P + 1) + p;
-          r_lo[j] = offs[0];
-          r_hi[j] = offs[1];
-        }
-      }
-    }
-    loaded = c0;
-  };
-  // A chunk: the runs of up to 64 * kRunsPerLane consecutive tiles of the
-  // wave's slice, lane l holding kRunsPerLane of them; pk[j] packs the start
-  // of the lane's run j among the lane's entries (< 3 tiles) with the run's
-  // offset in its tile (< 2^16); excl is the lane's first entry in the
-  // chunk, total the chunk's entries.
-  struct Chunk {
-    uint32_t pk[kRunsPerLane];
-    uint32_t excl, total;
-    uint64_t cbase;
-  };
-  auto chunk_of = [&](uint32_t c0) {
-    if (loaded != c0) load_runs(c0);
-    Chunk ch;
-    uint32_t lt = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < kRunsPerLane; ++j) {
-      ch.pk[j] = (lt << 16) | r_lo[j];
-      lt += r_hi[j] - r_lo[j];
-    }
-    uint32_t inc = lt;
-#pragma unroll
-    for (uint32_t off = 1; off < 64; off <<= 1) {
-      const uint32_t v = (uint32_t)__shfl_up((int)inc, off);
-      if (lane >= off) inc += v;
-    }
-    ch.excl = inc - lt;
-    ch.total = (uint32_t)__shfl((int)inc, 63);
-    ch.cbase = (uint64_t)c0 * tile;
-    return ch;
-  };
-  // The batch at entry e0 of a chunk: at[q] is the staging index of the
-  // lane's q-th entry, ev[q] whether it exists (absent entries point at a
-  // tile's first entry, so that every load stays branch-free and in
-  // bounds).  A batch takes the next 64 * kEntryBatch entries of the
-  // chunk's concatenated runs.
-  auto batch_of = [&](const Chunk& ch, uint32_t e0, uint64_t* at, bool* ev) {
-#pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      const uint32_t e = e0 + q * 64 + lane;
-      const uint32_t a = wave_upper_bound(ch.excl, e);
-      const uint32_t r = e - (uint32_t)__shfl((int)ch.excl, (int)a);
-      // the last of lane a's runs that starts at or before r holds it
-      uint32_t js = 0, ps = (uint32_t)__shfl((int)ch.pk[0], (int)a);
-#pragma unroll
-      for (uint32_t j = 1; j < kRunsPerLane; ++j) {
-        const uint32_t v = (uint32_t)__shfl((int)ch.pk[j], (int)a);
-        if ((v >> 16) <= r) {
-          js = j;
-          ps = v;
-        }
-      }
-      ev[q] = e < ch.total;
-      at[q] = ch.cbase + (ev[q] ? (uint64_t)(a * kRunsPerLane + js) * tile + (ps & 0xffffu) + (r - (ps >> 16))
-                                : 0ull);
-    }
-  };
-  // Calls body(at, ev, nb) for every batch of the wave's entries, in order
-  // (nb counts batches).
-  auto for_each_batch = [&](auto&& body) {
-    uint32_t nb = 0;
-    for (uint32_t c0 = w_lo; c0 < w_hi; c0 += 64 * kRunsPerLane) {
-      const Chunk ch = chunk_of(c0);
-      for (uint32_t e0 = 0; e0 < ch.total; e0 += 64 * kEntryBatch, ++nb) {
-        bool ev[kEntryBatch];
-        uint64_t at[kEntryBatch];
-        batch_of(ch, e0, at, ev);
-        body(at, ev, nb);
-      }
-    }
-    return nb;
-  };
+  RunReader<kWaves> rr(pv, p, P, ntiles);
 
   // keys first, then the first runs, then the wave's first batch of entries:
   // all in flight together, before the key table is built
@@ -644,15 +520,15 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     const uint32_t s = tid + j * kThreads;
     kk[j] = s < B ? tv.keys[base + s] : kEmpty;
   }
-  Chunk ch0{};
+  RunChunk ch0{};
   uint64_t at0[kEntryBatch];
   bool ev0[kEntryBatch];
   unsigned long long ek0[kEntryBatch];
   float4 v0[kEntryBatch];
   float q0[kEntryBatch];  // variance tables: the entries' squared-luminance sums
-  if (w_lo < w_hi) {
-    ch0 = chunk_of(w_lo);
-    batch_of(ch0, 0, at0, ev0);
+  if (rr.w_lo < rr.w_hi) {
+    ch0 = rr.chunk_of(rr.w_lo);
+    rr.batch_of(ch0, 0, at0, ev0);
 #pragma unroll
     for (uint32_t q = 0; q < kEntryBatch; ++q) {
       ek0[q] = pv.stage_key[at0[q]];
@@ -735,11 +611,11 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   };
   // the first batch was loaded above; every later one into the same registers
   uint32_t batches = 0;
-  for (uint32_t c0 = w_lo; c0 < w_hi; c0 += 64 * kRunsPerLane) {
-    const Chunk ch = c0 == w_lo ? ch0 : chunk_of(c0);
+  for (uint32_t c0 = rr.w_lo; c0 < rr.w_hi; c0 += 64 * kRunsPerLane) {
+    const RunChunk ch = c0 == rr.w_lo ? ch0 : rr.chunk_of(c0);
     for (uint32_t e0 = 0; e0 < ch.total; e0 += 64 * kEntryBatch, ++batches) {
-      if (c0 != w_lo || e0 != 0) {
-        batch_of(ch, e0, at0, ev0);
+      if (c0 != rr.w_lo || e0 != 0) {
+        rr.batch_of(ch, e0, at0, ev0);
 #pragma unroll
         for (uint32_t q = 0; q < kEntryBatch; ++q) {
           ek0[q] = pv.stage_key[at0[q]];
@@ -897,7 +773,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     }
     if (batches > kKeepBatches) {
       // later batches: read the keys again and find their (final) slots
-      for_each_batch([&](const uint64_t* at, const bool* ev, uint32_t nb) {
+      rr.for_each_batch([&](const uint64_t* at, const bool* ev, uint32_t nb) {
         if (nb < kKeepBatches) return;
         unsigned long long ek[kEntryBatch];
 #pragma unroll
@@ -1023,32 +899,7 @@ static size_t merge_lds(const TableView& tv) {
   return (size_t)(1u << tv.part_log2) * (8 + 4 + 24 + ((tv.var || weighted(tv)) ? 8 : 0) + 2);
 }
 
-// Raise a kernel's dynamic-LDS limit only as far as the launch needs (and
-// only when it exceeds the default 64 KiB).  The limit belongs to the
-// function on the current device; the largest value set is remembered per
-// device (devices past the table are set on every launch).
-constexpr int kLdsDevices = 64;
-struct LdsLimit {
-  std::atomic<int> bytes[kLdsDevices];
-};
-
-static hipError_t lds_limit(const void* fn, size_t bytes, LdsLimit* cur) {
-  if (bytes <= 65536) return hipSuccess;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const bool known = dev >= 0 && dev < kLdsDevices;
-  if (known && (int)bytes <= cur->bytes[dev].load(std::memory_order_relaxed)) return hipSuccess;
-  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess && known) {
-    int prev = cur->bytes[dev].load(std::memory_order_relaxed);
-    while ((int)bytes > prev && !cur->bytes[dev].compare_exchange_weak(prev, (int)bytes)) {
-    }
-  }
-  return e;
-}
-
-static bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n) {
+bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n) {
   return n <= pv.capacity && tv.part_log2 <= kMaxPartLog2 && pv.tile % kBinThreads == 0 &&
          bin_per_ok(pv.tile / kBinThreads) && (1u << (tv.log2_slots - tv.part_log2)) <= kTouchEntries;
 }
@@ -1090,6 +941,15 @@ hipError_t launch_bin(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const
   const size_t shm = bin_lds(P, per);
   const uint32_t x = record_extras(rec);
   if ((x & kXWeight) && !weighted(tv)) return hipErrorInvalidValue;
+  if (tv.sh) {
+    if (per != 8 || !pv.stage_n || pv.perm) return hipErrorInvalidValue;
+    switch (x) {
+      case 0: return launch_bin_t<8, kXNormal>(rec, n, kp, tv, pv, shm, ntiles, s);
+      case kXFootprint: return launch_bin_t<8, kXNormal | kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
+      case kXWeight: return launch_bin_t<8, kXNormal | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+      default: return launch_bin_t<8, kXNormal | kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    }
+  }
   if (per == 8) return launch_bin_x<8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
   if (per == 12) return launch_bin_x<12>(x, rec, n, kp, tv, pv, shm, ntiles, s);
   return launch_bin_x<16>(x, rec, n, kp, tv, pv, shm, ntiles, s);
