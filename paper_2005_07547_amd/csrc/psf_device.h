@@ -432,6 +432,10 @@ __device__ __forceinline__ uint8_t lookup_finish(const TableView& tv, int32_t dt
 // reads: non-temporal, so streaming them does not evict from the caches the
 // table the pass gathers from.
 __device__ __forceinline__ float ld_once(const float* p) { return __builtin_nontemporal_load(p); }
+// (p wave-uniform, i < 2^30: a scalar address and a 32-bit offset)
+__device__ __forceinline__ float ld_once_at(const float* p, uint32_t i) {
+  return __builtin_nontemporal_load(reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + (i << 2)));
+}
 __device__ __forceinline__ void st_once(float* p, float v) { __builtin_nontemporal_store(v, p); }
 
 // Key of query i of a structure-of-arrays query set (kEmpty if rejected).

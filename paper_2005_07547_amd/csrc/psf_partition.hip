@@ -38,7 +38,15 @@
 
 namespace psf {
 
-constexpr int kBinThreads = 512;
+// Threads and records per thread of the binning pass: a tile of 4096 records
+// takes 1024 threads with 4 records each (6144: 768 with 8, weighted 512
+// with 12; 8192: 1024 with 8).  The pass waits on one dependent step after
+// another (record loads, LDS ranks, scan, staging), so twice the wavefronts
+// with half the records each hide more of it: 70.6 -> 62.0 us for 3,686,400
+// records (900 tiles) against 512 threads with 8, 174 -> 163 us for 1688
+// tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
+// (one of 8192 records, by its LDS).
+constexpr int bin_waves(uint32_t threads, uint32_t per) { return threads * per > 6144 ? 4 : (int)threads / 128; }
 constexpr int kMergeThreads = 512;
 constexpr uint32_t kMaxPartLog2 = 12;
 
@@ -48,8 +56,8 @@ bool bin_per_ok(uint32_t per) { return per == 8 || per == 12 || per == 16; }
 // in one float4 pass) where two blocks per CU still fit, else 12 (a tile
 // with more than 3/4 of its records as entries stages its values in two
 // halves).
-__host__ __device__ constexpr size_t bin_lds_per_record(uint32_t per) { return per <= 8 ? 16 : 12; }
-uint32_t bin_tile(uint32_t per) { return kBinThreads * per; }
+__host__ __device__ constexpr size_t bin_lds_per_record(uint32_t tile) { return tile <= 4096 ? 16 : 12; }
+uint32_t bin_tile(uint32_t per) { return 512 * per; }
 
 // Exclusive prefix sum of cnt[0..m) in LDS, in place; returns the total.
 // Called by all kThreads threads of the block.
@@ -137,26 +145,26 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
   return 63u - (uint32_t)__builtin_clzll(~cont & upto);
 }
 
-template <uint32_t kPer, uint32_t kX>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
 __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const KeyParams& kp,
                                          const TableView& tv, const PartView& pv, uint32_t tile) {
   constexpr bool kFp = (kX & kXFootprint) != 0, kW = (kX & kXWeight) != 0, kN = (kX & kXNormal) != 0;
   extern __shared__ uint32_t s_dyn_bin[];
-  __shared__ uint32_t s_wave[kBinThreads / 64 + 1];
-  __shared__ unsigned long long s_cont[kBinThreads / 64][kPer];  // per wave and record row: run continuations
+  __shared__ uint32_t s_wave[kThreads / 64 + 1];
+  __shared__ unsigned long long s_cont[kThreads / 64][kPer];  // per wave and record row: run continuations
   const uint32_t P = 1u << (tv.log2_slots - tv.part_log2);
   uint32_t* s_hist = s_dyn_bin;
   unsigned long long* s_k = reinterpret_cast<unsigned long long*>(s_dyn_bin);
   const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
-  const uint64_t t0 = (uint64_t)tile * (kBinThreads * kPer);
+  const uint64_t t0 = (uint64_t)tile * (kThreads * kPer);
   // records merge into runs only with integer counters and no weights; a
   // table that keeps the variance also sums each run's squared luminances
   // (in registers: with 8 records per thread; with more, its records stay
   // entries of their own)
   const bool var = tv.var != nullptr;
-  constexpr bool kQRuns = kPer <= 8;
+  constexpr bool kQRuns = kThreads * kPer <= 4096;
   const bool premerge = !kW && !kN && (kQRuns || !var);
-  for (uint32_t p = tid; p <= P; p += kBinThreads) s_hist[p] = 0;
+  for (uint32_t p = tid; p <= P; p += kThreads) s_hist[p] = 0;
   __syncthreads();
 
   uint64_t key[kPer];
@@ -178,34 +186,46 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   // memory round trip; validity is applied afterwards.  The records are read
   // once: non-temporal loads keep them from evicting what the merge pass
   // reads next from the caches (the staged entries, the key mirror, the
-  // slots).
-  const float* p_ox = hr ? rec.ox : rec.px;
-  const float* p_oy = hr ? rec.oy : rec.px;
-  const float* p_oz = hr ? rec.oz : rec.px;
-  const float* p_ro = hr ? rec.rough : rec.px;
-  constexpr uint32_t kLoad = kPer == 12 ? 3 : 4;  // records per load round trip (12: no spills)
+  // slots).  The tile's first element of each array is a scalar address and
+  // a record's offset from it one 32-bit register for every array.
+  const uint32_t m = n - t0 < kThreads * kPer ? (uint32_t)(n - t0) : kThreads * kPer;  // the tile's records
+  const float* const p_px = rec.px + t0;
+  const float* const p_py = rec.py + t0;
+  const float* const p_pz = rec.pz + t0;
+  const float* const p_nx = rec.nx + t0;
+  const float* const p_ny = rec.ny + t0;
+  const float* const p_nz = rec.nz + t0;
+  const float* const p_ox = (hr ? rec.ox : rec.px) + t0;
+  const float* const p_oy = (hr ? rec.oy : rec.px) + t0;
+  const float* const p_oz = (hr ? rec.oz : rec.px) + t0;
+  const float* const p_ro = (hr ? rec.rough : rec.px) + t0;
+  const float* const p_r = rec.r + t0;
+  const float* const p_g = rec.g + t0;
+  const float* const p_b = rec.b + t0;
+  const float* const p_fp = (kFp ? rec.footprint : rec.px) + t0;
+  constexpr uint32_t kLoad = kPer < 2 ? 1 : 2;  // records per load round trip
 #pragma unroll
   for (uint32_t j0 = 0; j0 < kPer; j0 += kLoad) {
     float f[kLoad][13];
     float fp[kLoad];
 #pragma unroll
     for (uint32_t q = 0; q < kLoad; ++q) {
-      const uint64_t i = t0 + (uint64_t)(j0 + q) * kBinThreads + tid;
-      const uint64_t ic = i < n ? i : n - 1;
-      f[q][0] = __builtin_nontemporal_load(rec.px + ic);
-      f[q][1] = __builtin_nontemporal_load(rec.py + ic);
-      f[q][2] = __builtin_nontemporal_load(rec.pz + ic);
-      f[q][3] = __builtin_nontemporal_load(rec.nx + ic);
-      f[q][4] = __builtin_nontemporal_load(rec.ny + ic);
-      f[q][5] = __builtin_nontemporal_load(rec.nz + ic);
-      f[q][6] = __builtin_nontemporal_load(p_ox + ic);
-      f[q][7] = __builtin_nontemporal_load(p_oy + ic);
-      f[q][8] = __builtin_nontemporal_load(p_oz + ic);
-      f[q][9] = __builtin_nontemporal_load(rec.r + ic);
-      f[q][10] = __builtin_nontemporal_load(rec.g + ic);
-      f[q][11] = __builtin_nontemporal_load(rec.b + ic);
-      f[q][12] = __builtin_nontemporal_load(p_ro + ic);
-      fp[q] = kFp ? __builtin_nontemporal_load(rec.footprint + ic) : 0.0f;
+      const uint32_t il = (j0 + q) * kThreads + tid;
+      const uint32_t ic = il < m ? il : m - 1;
+      f[q][0] = ld_once_at(p_px, ic);
+      f[q][1] = ld_once_at(p_py, ic);
+      f[q][2] = ld_once_at(p_pz, ic);
+      f[q][3] = ld_once_at(p_nx, ic);
+      f[q][4] = ld_once_at(p_ny, ic);
+      f[q][5] = ld_once_at(p_nz, ic);
+      f[q][6] = ld_once_at(p_ox, ic);
+      f[q][7] = ld_once_at(p_oy, ic);
+      f[q][8] = ld_once_at(p_oz, ic);
+      f[q][9] = ld_once_at(p_r, ic);
+      f[q][10] = ld_once_at(p_g, ic);
+      f[q][11] = ld_once_at(p_b, ic);
+      f[q][12] = ld_once_at(p_ro, ic);
+      fp[q] = kFp ? ld_once_at(p_fp, ic) : 0.0f;
     }
     // Every loaded value is used here, so the batch's loads all issue
     // before the first wait: left alone, the compiler sinks some of them
@@ -220,17 +240,17 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
 #pragma unroll
     for (uint32_t q = 0; q < kLoad; ++q) {
       const uint32_t j = j0 + q;
-      const uint64_t i = t0 + (uint64_t)j * kBinThreads + tid;
+      const bool in = j * kThreads + tid < m;
       bool ovf = false;
       uint64_t k = 0;
-      const bool kv = i < n && cell_key(kp, f[q][0], f[q][1], f[q][2], f[q][3], f[q][4], f[q][5], f[q][6],
+      const bool kv = in && cell_key(kp, f[q][0], f[q][1], f[q][2], f[q][3], f[q][4], f[q][5], f[q][6],
                                         f[q][7], f[q][8], hr, f[q][12], kFp, fp[q], k, ovf);
       const bool sv = finite3(f[q][9], f[q][10], f[q][11]);
       key[j] = (kv && sv) ? k : k | kLookupOnlyBit;
       rgb[j][0] = f[q][9];
       rgb[j][1] = f[q][10];
       rgb[j][2] = f[q][11];
-      if (i < n && !(kv && sv)) ++n_skip;
+      if (in && !(kv && sv)) ++n_skip;
       n_ovf += (kv && sv && ovf) ? 1u : 0u;
       // a record whose sample is rejected but whose key is valid is still a
       // query vertex: with the fused query it is staged for lookup only
@@ -304,10 +324,10 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   };
   if (!kW) count_events();
   __syncthreads();
-  const uint32_t count = block_exclusive_scan<kBinThreads>(s_hist, P + 1, s_wave);
+  const uint32_t count = block_exclusive_scan<kThreads>(s_hist, P + 1, s_wave);
 
   uint32_t* offs = pv.runs + (uint64_t)tile * (P + 1);
-  for (uint32_t p = tid; p <= P; p += kBinThreads) offs[p] = s_hist[p];
+  for (uint32_t p = tid; p <= P; p += kThreads) offs[p] = s_hist[p];
 #pragma unroll
   for (uint32_t j = 0; j < kPer; ++j) {
     if (pos[j] != ~0u && !(pos[j] & kPosTail)) {
@@ -324,10 +344,11 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
     }
   }
   if (pv.perm) {
+    uint16_t* const perm = pv.perm + t0;
 #pragma unroll
     for (uint32_t j = 0; j < kPer; ++j) {
-      const uint64_t i = t0 + (uint64_t)j * kBinThreads + tid;
-      if (i < n) pv.perm[i] = pos[j] != ~0u ? (uint16_t)(pos[j] & kPosBits) : kNoPos;
+      const uint32_t i = j * kThreads + tid;
+      if (i < m) perm[i] = pos[j] != ~0u ? (uint16_t)(pos[j] & kPosBits) : kNoPos;
     }
   }
   __syncthreads();  // the histogram is dead from here on; its LDS becomes staging
@@ -363,7 +384,7 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
 #pragma unroll
     for (uint32_t j = 0; j < kPer; ++j) {
       if (!own_entry(j)) continue;
-      const uint64_t i = t0 + (uint64_t)j * kBinThreads + tid;
+      const uint64_t i = t0 + (uint64_t)j * kThreads + tid;
       pv.stage_n[t0 + (pos[j] & kPosBits)] = make_float4(rec.nx[i], rec.ny[i], rec.nz[i], 0.0f);
     }
   }
@@ -378,7 +399,7 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
     for (uint32_t j = 0; j < kPer; ++j) {
       wn[j] = 0.0f;
       if (!own_entry(j)) continue;
-      const float w = rec.weight[t0 + (uint64_t)j * kBinThreads + tid];
+      const float w = rec.weight[t0 + (uint64_t)j * kThreads + tid];
       if (pos[j] & kPosLookupOnly) continue;
       if (__builtin_isfinite(w) && w > 0.0f) {
         if (!kN) {  // (the SH sums weight the sample themselves, in binary64)
@@ -398,19 +419,19 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   for (uint32_t j = 0; j < kPer; ++j)
     if (own_entry(j)) s_k[pos[j] & kPosBits] = key[j];
   __syncthreads();
-  for (uint32_t i = tid; i < count; i += kBinThreads) pv.stage_key[t0 + i] = s_k[i];
+  for (uint32_t i = tid; i < count; i += kThreads) pv.stage_key[t0 + i] = s_k[i];
   __syncthreads();
   // the entries' values {r, g, b, n}: as float4 when they fit in the LDS,
   // else in two halves, (r, g) then (b, n)
   auto entry_w = [&](uint32_t j) { return kW ? wn[kW ? j : 0] : (float)entry_n(j); };
-  const size_t lds_bytes = (size_t)kBinThreads * kPer * bin_lds_per_record(kPer);  // the launch's dynamic LDS
+  const size_t lds_bytes = (size_t)kThreads * kPer * bin_lds_per_record(kThreads * kPer);  // the launch's dynamic LDS
   if ((size_t)count * 16 <= lds_bytes) {
     float4* s_v = reinterpret_cast<float4*>(s_dyn_bin);
 #pragma unroll
     for (uint32_t j = 0; j < kPer; ++j)
       if (own_entry(j)) s_v[pos[j] & kPosBits] = make_float4(rgb[j][0], rgb[j][1], rgb[j][2], entry_w(j));
     __syncthreads();
-    for (uint32_t i = tid; i < count; i += kBinThreads) pv.stage_v[t0 + i] = s_v[i];
+    for (uint32_t i = tid; i < count; i += kThreads) pv.stage_v[t0 + i] = s_v[i];
   } else {
     float2* s_v = reinterpret_cast<float2*>(s_dyn_bin);
     float2* dst = reinterpret_cast<float2*>(pv.stage_v + t0);
@@ -418,22 +439,20 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
     for (uint32_t j = 0; j < kPer; ++j)
       if (own_entry(j)) s_v[pos[j] & kPosBits] = make_float2(rgb[j][0], rgb[j][1]);
     __syncthreads();
-    for (uint32_t i = tid; i < count; i += kBinThreads) dst[2 * i] = s_v[i];
+    for (uint32_t i = tid; i < count; i += kThreads) dst[2 * i] = s_v[i];
     __syncthreads();
 #pragma unroll
     for (uint32_t j = 0; j < kPer; ++j)
       if (own_entry(j)) s_v[pos[j] & kPosBits] = make_float2(rgb[j][2], entry_w(j));
     __syncthreads();
-    for (uint32_t i = tid; i < count; i += kBinThreads) dst[2 * i + 1] = s_v[i];
+    for (uint32_t i = tid; i < count; i += kThreads) dst[2 * i + 1] = s_v[i];
   }
 }
 
-// Two 512-thread blocks per CU need at most 128 VGPRs (four waves per SIMD);
-// the instantiations with footprints or weights would take a few more.
-template <uint32_t kPer, uint32_t kX>
-__global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_eu(kPer <= 12 ? 4 : 1)))
+template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer))))
 k_bin(RecPtrs rec, uint64_t n, KeyParams kp, TableView tv, PartView pv) {
-  bin_body<kPer, kX>(rec, n, kp, tv, pv, blockIdx.x);
+  bin_body<kThreads, kPer, kX>(rec, n, kp, tv, pv, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ run table transpose
@@ -886,8 +905,8 @@ __global__ void __launch_bounds__(kUnstageThreads) k_unstage(PartView pv, uint32
 }
 
 // ------------------------------------------------------------------ launchers
-static size_t bin_lds(uint32_t P, uint32_t per) {
-  const size_t hist = (size_t)(P + 1) * 4, stage = (size_t)kBinThreads * per * bin_lds_per_record(per);
+static size_t bin_lds(uint32_t P, uint32_t tile) {
+  const size_t hist = (size_t)(P + 1) * 4, stage = (size_t)tile * bin_lds_per_record(tile);
   return hist > stage ? hist : stage;
 }
 
@@ -900,29 +919,29 @@ static size_t merge_lds(const TableView& tv) {
 }
 
 bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n) {
-  return n <= pv.capacity && tv.part_log2 <= kMaxPartLog2 && pv.tile % kBinThreads == 0 &&
-         bin_per_ok(pv.tile / kBinThreads) && (1u << (tv.log2_slots - tv.part_log2)) <= kTouchEntries;
+  return n <= pv.capacity && tv.part_log2 <= kMaxPartLog2 && pv.tile % 512 == 0 &&
+         bin_per_ok(pv.tile / 512) && (1u << (tv.log2_slots - tv.part_log2)) <= kTouchEntries;
 }
 
-template <uint32_t kPer, uint32_t kX>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
 static hipError_t launch_bin_t(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const TableView& tv,
                                const PartView& pv, size_t shm, uint32_t ntiles, hipStream_t s) {
   static LdsLimit lim;  // one per instantiation
-  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_bin<kPer, kX>), shm, &lim);
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_bin<kThreads, kPer, kX>), shm, &lim);
   if (e != hipSuccess) return e;
-  k_bin<kPer, kX><<<ntiles, kBinThreads, shm, s>>>(rec, n, kp, tv, pv);
+  k_bin<kThreads, kPer, kX><<<ntiles, kThreads, shm, s>>>(rec, n, kp, tv, pv);
   return hipGetLastError();
 }
 
-template <uint32_t kPer>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kThreadsW = kThreads, uint32_t kPerW = kPer>
 static hipError_t launch_bin_x(uint32_t x, const RecPtrs& rec, uint64_t n, const KeyParams& kp,
                                const TableView& tv, const PartView& pv, size_t shm, uint32_t ntiles,
                                hipStream_t s) {
   switch (x) {
-    case 0: return launch_bin_t<kPer, 0>(rec, n, kp, tv, pv, shm, ntiles, s);
-    case kXFootprint: return launch_bin_t<kPer, kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
-    case kXWeight: return launch_bin_t<kPer, kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
-    default: return launch_bin_t<kPer, kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case 0: return launch_bin_t<kThreads, kPer, 0>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case kXFootprint: return launch_bin_t<kThreads, kPer, kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case kXWeight: return launch_bin_t<kThreadsW, kPerW, kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    default: return launch_bin_t<kThreadsW, kPerW, kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
   }
 }
 
@@ -936,23 +955,23 @@ hipError_t launch_bin(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const
   if (n == 0) return hipSuccess;
   if (!partition_ok(tv, pv, n)) return hipErrorInvalidValue;
   const uint32_t P = 1u << (tv.log2_slots - tv.part_log2);
-  const uint32_t per = pv.tile / kBinThreads;
+  const uint32_t per = pv.tile / 512;
   const uint32_t ntiles = (uint32_t)((n + pv.tile - 1) / pv.tile);
-  const size_t shm = bin_lds(P, per);
+  const size_t shm = bin_lds(P, pv.tile);
   const uint32_t x = record_extras(rec);
   if ((x & kXWeight) && !weighted(tv)) return hipErrorInvalidValue;
   if (tv.sh) {
     if (per != 8 || !pv.stage_n || pv.perm) return hipErrorInvalidValue;
     switch (x) {
-      case 0: return launch_bin_t<8, kXNormal>(rec, n, kp, tv, pv, shm, ntiles, s);
-      case kXFootprint: return launch_bin_t<8, kXNormal | kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
-      case kXWeight: return launch_bin_t<8, kXNormal | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
-      default: return launch_bin_t<8, kXNormal | kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+      case 0: return launch_bin_t<1024, 4, kXNormal>(rec, n, kp, tv, pv, shm, ntiles, s);
+      case kXFootprint: return launch_bin_t<1024, 4, kXNormal | kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
+      case kXWeight: return launch_bin_t<1024, 4, kXNormal | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+      default: return launch_bin_t<1024, 4, kXNormal | kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
     }
   }
-  if (per == 8) return launch_bin_x<8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
-  if (per == 12) return launch_bin_x<12>(x, rec, n, kp, tv, pv, shm, ntiles, s);
-  return launch_bin_x<16>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+  if (per == 8) return launch_bin_x<1024, 4>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+  if (per == 12) return launch_bin_x<768, 8, 512, 12>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+  return launch_bin_x<1024, 8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
 }
 
 hipError_t launch_merge(uint64_t n, const TableView& tv, const PartView& pv, const BlendParams* fuse,
@@ -1050,7 +1069,7 @@ __global__ void __launch_bounds__(kTransposeThreads) k_transpose_batch(const Bat
 
 // kX: the union of the sessions' record extras; each session runs the body
 // of its own.
-template <uint32_t kPer, uint32_t kW, uint32_t kFpAllowed>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kW, uint32_t kFpAllowed>
 __device__ __forceinline__ void bin_session(const BatchSession& S, uint32_t local) {
   const RecPtrs rec = S.rec;
   const KeyParams kp = S.kp;
@@ -1058,26 +1077,26 @@ __device__ __forceinline__ void bin_session(const BatchSession& S, uint32_t loca
   const PartView pv = S.pv;
   const uint64_t n = S.n;
   if (kFpAllowed && rec.footprint)
-    bin_body<kPer, kW | kXFootprint>(rec, n, kp, tv, pv, local);
+    bin_body<kThreads, kPer, kW | kXFootprint>(rec, n, kp, tv, pv, local);
   else
-    bin_body<kPer, kW>(rec, n, kp, tv, pv, local);
+    bin_body<kThreads, kPer, kW>(rec, n, kp, tv, pv, local);
 }
 
 // (the batch instantiations that carry several bodies would spill heavily
 // under the same cap)
-template <uint32_t kPer, uint32_t kX>
-__global__ void __launch_bounds__(kBinThreads) __attribute__((amdgpu_waves_per_eu(kPer <= 12 && kX == 0 ? 4 : 1)))
+template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer))))
 k_bin_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
   const BatchSession& S = ss[find_session(bg, k, blockIdx.x)];
   const uint32_t local = blockIdx.x - S.tile_begin;
   if (local >= S.ntiles) return;
   if constexpr ((kX & kXWeight) != 0) {
     if (S.rec.weight) {
-      bin_session<kPer, kXWeight, kX & kXFootprint>(S, local);
+      bin_session<kThreads, kPer, kXWeight, kX & kXFootprint>(S, local);
       return;
     }
   }
-  bin_session<kPer, 0, kX & kXFootprint>(S, local);
+  bin_session<kThreads, kPer, 0, kX & kXFootprint>(S, local);
 }
 
 // 1024 threads per block when the widest session's partitions leave room
@@ -1121,24 +1140,24 @@ __global__ void __launch_bounds__(kQueryBlock) k_query_batch(const BatchSession*
   if (found) found[i] = hit;
 }
 
-template <uint32_t kPer, uint32_t kX>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
 static hipError_t launch_bin_batch_t(const BatchSession* d_ss, const uint32_t* bg, uint32_t k, uint32_t tiles,
                                      size_t lds, hipStream_t s) {
   static LdsLimit lim;  // one per instantiation
-  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_bin_batch<kPer, kX>), lds, &lim);
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_bin_batch<kThreads, kPer, kX>), lds, &lim);
   if (e != hipSuccess) return e;
-  k_bin_batch<kPer, kX><<<tiles, kBinThreads, lds, s>>>(d_ss, bg, k);
+  k_bin_batch<kThreads, kPer, kX><<<tiles, kThreads, lds, s>>>(d_ss, bg, k);
   return hipGetLastError();
 }
 
-template <uint32_t kPer>
+template <uint32_t kThreads, uint32_t kPer, uint32_t kThreadsW = kThreads, uint32_t kPerW = kPer>
 static hipError_t launch_bin_batch_x(uint32_t x, const BatchSession* d_ss, const uint32_t* bg, uint32_t k,
                                      uint32_t tiles, size_t lds, hipStream_t s) {
   switch (x) {
-    case 0: return launch_bin_batch_t<kPer, 0>(d_ss, bg, k, tiles, lds, s);
-    case kXFootprint: return launch_bin_batch_t<kPer, kXFootprint>(d_ss, bg, k, tiles, lds, s);
-    case kXWeight: return launch_bin_batch_t<kPer, kXWeight>(d_ss, bg, k, tiles, lds, s);
-    default: return launch_bin_batch_t<kPer, kXFootprint | kXWeight>(d_ss, bg, k, tiles, lds, s);
+    case 0: return launch_bin_batch_t<kThreads, kPer, 0>(d_ss, bg, k, tiles, lds, s);
+    case kXFootprint: return launch_bin_batch_t<kThreads, kPer, kXFootprint>(d_ss, bg, k, tiles, lds, s);
+    case kXWeight: return launch_bin_batch_t<kThreadsW, kPerW, kXWeight>(d_ss, bg, k, tiles, lds, s);
+    default: return launch_bin_batch_t<kThreadsW, kPerW, kXFootprint | kXWeight>(d_ss, bg, k, tiles, lds, s);
   }
 }
 
@@ -1149,7 +1168,7 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   uint32_t tiles = 0, parts = 0, qblks = 0, trans = 0;
   size_t lds_b = 0, lds_m = 0, lds_q = 0;
   uint32_t x = 0;  // what any session's records carry
-  const uint32_t per = h_ss[0].pv.tile / kBinThreads;
+  const uint32_t per = h_ss[0].pv.tile / 512;
   for (uint32_t i = 0; i < k; ++i) {
     const BatchSession& S = h_ss[i];
     if (h_begins[i] != S.tile_begin || h_begins[stride + i] != S.part_begin ||
@@ -1161,7 +1180,7 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
         S.ntrans != (S.pv.runs_t ? transpose_blocks(S.ntiles, 1u << (S.tv.log2_slots - S.tv.part_log2)) : 0u))
       return hipErrorInvalidValue;
     const uint32_t P = 1u << (S.tv.log2_slots - S.tv.part_log2);
-    const size_t lb = bin_lds(P, per), lm = merge_lds(S.tv);
+    const size_t lb = bin_lds(P, S.pv.tile), lm = merge_lds(S.tv);
     lds_b = lb > lds_b ? lb : lds_b;
     lds_m = lm > lds_m ? lm : lds_m;
     if ((S.fused_query != 0) != (S.pv.perm != nullptr)) return hipErrorInvalidValue;
@@ -1183,9 +1202,9 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   const uint32_t* bg_part = d_begins + stride;
   const uint32_t* bg_qblk = d_begins + 2 * stride;
   const uint32_t* bg_trans = d_begins + 3 * stride;
-  hipError_t e = per == 8    ? launch_bin_batch_x<8>(x, d_ss, bg_tile, k, tiles, lds_b, s)
-                  : per == 12 ? launch_bin_batch_x<12>(x, d_ss, bg_tile, k, tiles, lds_b, s)
-                              : launch_bin_batch_x<16>(x, d_ss, bg_tile, k, tiles, lds_b, s);
+  hipError_t e = per == 8    ? launch_bin_batch_x<1024, 4>(x, d_ss, bg_tile, k, tiles, lds_b, s)
+                  : per == 12 ? launch_bin_batch_x<768, 8, 512, 12>(x, d_ss, bg_tile, k, tiles, lds_b, s)
+                              : launch_bin_batch_x<1024, 8>(x, d_ss, bg_tile, k, tiles, lds_b, s);
   if (e != hipSuccess) return e;
   e = wide ? lds_limit(reinterpret_cast<const void*>(&k_merge_batch<1024>), lds_m, &lim_m[1])
            : lds_limit(reinterpret_cast<const void*>(&k_merge_batch<kMergeThreads>), lds_m, &lim_m[0]);
