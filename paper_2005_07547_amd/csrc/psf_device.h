@@ -194,19 +194,19 @@ __device__ __forceinline__ ProbeSeq probe_seq(uint64_t key, uint32_t log2_slots,
 #pragma clang fp contract(off)
 
 __device__ __forceinline__ bool finite3(float a, float b, float c) {
-  return __builtin_isfinite(a) && __builtin_isfinite(b) && __builtin_isfinite(c);
+  return (int)__builtin_isfinite(a) & (int)__builtin_isfinite(b) & (int)__builtin_isfinite(c);
 }
 
 // Level: floor(log2(kappa * d^2) / 2) clamped, read off the binary32 exponent.
 __device__ __forceinline__ int32_t cell_level(const KeyParams& kp, float px, float py, float pz) {
-  if (kp.kappa == 0.0f) return 0;
   const float dx = px - kp.cx, dy = py - kp.cy, dz = pz - kp.cz;
   const float d2 = (dx * dx + dy * dy) + dz * dz;
   const float q = d2 * kp.kappa;
   const int32_t biased = (int32_t)((__float_as_uint(q) >> 23) & 0xffu);
   const int32_t e = biased ? biased - 127 : -127;
   const int32_t lvl = e >> 1;  // arithmetic shift: floor(e / 2)
-  return lvl < 0 ? 0 : (lvl > kp.max_level ? kp.max_level : lvl);
+  const int32_t most = kp.kappa == 0.0f ? 0 : kp.max_level;
+  return lvl < 0 ? 0 : (lvl > most ? most : lvl);
 }
 
 // Level from a path footprint (the world-space width a path covers at the
@@ -220,67 +220,97 @@ __device__ __forceinline__ int32_t footprint_level(const KeyParams& kp, float fp
   return lvl < 0 ? 0 : (lvl > kp.max_level ? kp.max_level : lvl);
 }
 
-// floor(p * 2^-shift) modulo 2^16, flagging values outside [-2^15, 2^15).
-__device__ __forceinline__ uint32_t grid16(float p, int32_t shift, bool& ovf) {
-  float f = floorf(ldexpf(p, -shift));
-  ovf |= !(f >= -32768.0f && f < 32768.0f);
-  f = fminf(fmaxf(f, -2147483648.0f), 2147483520.0f);
-  return (uint32_t)(int32_t)f & 0xffffu;
+// floor(p * 2^-shift) modulo 2^16; f receives the floor itself.
+__device__ __forceinline__ uint32_t grid16(float p, int32_t shift, float& f) {
+  f = floorf(ldexpf(p, -shift));
+  return (uint32_t)(int32_t)fminf(fmaxf(f, -2147483648.0f), 2147483520.0f) & 0xffffu;
 }
 
-// Octahedral map of a direction onto a B x B grid (B = 2^b): index iu*B + iw.
+// Octahedral map of a direction onto a B x B grid (B = 2^b): index iu*B + iw,
+// where with l1 = (|x| + |y|) + |z|, u = x / l1 and w = y / l1 (correctly
+// rounded; 0 if l1 is 0), folded over for z < 0, iu = min(floor((u / 2 + 1 / 2)
+// B), B - 1) and likewise iw.
+//
+// Both quotients share one reciprocal: after a Newton step on it, each takes
+// two remainder corrections, the last from a remainder that is exact, so it
+// is the correctly rounded quotient wherever nothing underflows.  That holds
+// for l1 in [2^-60, 2^60] and numerators above 2^-100; below those u is so
+// small that it rounds away against 1 or 1 / 2.  A wave with a lane outside
+// that range of l1 (scaled first, by a power of two) takes one more branch.
+// The fold's sign is that of the rounded u, which is +0 or -0 (counted as
+// positive) where |x| <= l1 2^-150.
 __device__ __forceinline__ uint32_t octa_bin(float x, float y, float z, int32_t b) {
-  const float B = (float)(1 << b);
-  const int32_t top = (1 << b) - 1;
   const float l1 = (fabsf(x) + fabsf(y)) + fabsf(z);
-  float u = 0.0f, w = 0.0f;
-  if (l1 > 0.0f) {
-    u = x / l1;
-    w = y / l1;
+  float xs = x, ys = y, ls = l1;
+  if (__ballot(!(l1 >= 0x1p-60f && l1 <= 0x1p60f))) {
+    int32_t e = 0;
+    (void)frexpf(l1, &e);
+    xs = ldexpf(x, -e);
+    ys = ldexpf(y, -e);
+    ls = ldexpf(l1, -e);
+    if (!(l1 > 0.0f && l1 <= 3.402823466e38f)) {  // all zero, or the sum overflowed
+      xs = ys = 0.0f;
+      ls = 1.0f;
+    }
   }
-  if (z < 0.0f) {
-    const float fu = (1.0f - fabsf(w)) * (u >= 0.0f ? 1.0f : -1.0f);
-    const float fw = (1.0f - fabsf(u)) * (w >= 0.0f ? 1.0f : -1.0f);
-    u = fu;
-    w = fw;
-  }
-  int32_t iu = (int32_t)floorf((u * 0.5f + 0.5f) * B);
-  int32_t iw = (int32_t)floorf((w * 0.5f + 0.5f) * B);
-  iu = iu < 0 ? 0 : (iu > top ? top : iu);
-  iw = iw < 0 ? 0 : (iw > top ? top : iw);
-  return (uint32_t)(iu * (1 << b) + iw);
+  const float r0 = __builtin_amdgcn_rcpf(ls);
+  const float rc = __builtin_fmaf(__builtin_fmaf(-ls, r0, 1.0f), r0, r0);
+  auto quotient = [&](float n) {
+    float q = n * rc;
+    q = __builtin_fmaf(__builtin_fmaf(-ls, q, n), rc, q);
+    return __builtin_fmaf(__builtin_fmaf(-ls, q, n), rc, q);
+  };
+  const float u = quotient(xs), w = quotient(ys);
+  const float tiny = -(l1 * 0x1p-50f);
+  const float fu = copysignf(1.0f - fabsf(w), x * 0x1p100f >= tiny ? 1.0f : -1.0f);
+  const float fw = copysignf(1.0f - fabsf(u), y * 0x1p100f >= tiny ? 1.0f : -1.0f);
+  const bool fold = z < 0.0f;
+  // (u / 2 + 1 / 2) B = u B / 2 + B / 2, rounded once either way; in [0, B]
+  const float h = 0.5f * (float)(1 << b);
+  const uint32_t top = (1u << b) - 1u;
+  const uint32_t iu = (uint32_t)__builtin_fmaf(fold ? fu : u, h, h);
+  const uint32_t iw = (uint32_t)__builtin_fmaf(fold ? fw : w, h, h);
+  return ((iu < top ? iu : top) << b) + (iw < top ? iw : top);
 }
 
 // Cell key of one vertex.  Returns false for rejected (non-finite) input.
 // has_rough is false when the caller supplied no roughness array (every
-// vertex diffuse); the direction is read only for glossy vertices.  With a
+// vertex diffuse); the direction is used only for glossy vertices.  With a
 // footprint (has_fp) the level comes from it (it must be finite and > 0),
 // else from the camera distance.  up > 0 asks for the cell that many levels
 // coarser (false if that passes max_level).
+//
+// The key decides nothing by branches on the lane's values: it is computed
+// for every lane, rejected ones too, and rejected at the end.  With early
+// exits (and four divisions) it took 212 vector instructions in 15 exec-mask
+// regions, and its scalar masks spilled in the binning pass.
 __device__ __forceinline__ bool cell_key(const KeyParams& kp, float px, float py, float pz, float nx,
                                          float ny, float nz, float ox, float oy, float oz,
                                          bool has_rough, float rough, bool has_fp, float fp,
                                          uint64_t& key, bool& ovf, int32_t up = 0) {
-  if (!finite3(px, py, pz) || !finite3(nx, ny, nz)) return false;
-  if (has_fp && !(__builtin_isfinite(fp) && fp > 0.0f)) return false;
-  bool glossy = false;
-  if (has_rough) {
-    if (!__builtin_isfinite(rough)) return false;
-    glossy = rough < kp.rough_thr;
-    if (glossy && !finite3(ox, oy, oz)) return false;
+  int ok = (int)finite3(px, py, pz) & (int)finite3(nx, ny, nz);
+  int32_t lvl;
+  if (has_fp) {
+    ok &= (int)__builtin_isfinite(fp) & (int)(fp > 0.0f);
+    lvl = footprint_level(kp, fp);
+  } else {
+    lvl = cell_level(kp, px, py, pz);
   }
-  const int32_t lvl = (has_fp ? footprint_level(kp, fp) : cell_level(kp, px, py, pz)) + up;
-  if (lvl > kp.max_level) return false;
+  lvl += up;
+  if (up > 0) ok &= (int)(lvl <= kp.max_level);
   const int32_t shift = kp.e_min + lvl;
-  ovf = false;
-  const uint64_t ix = grid16(px, shift, ovf);
-  const uint64_t iy = grid16(py, shift, ovf);
-  const uint64_t iz = grid16(pz, shift, ovf);
-  const uint64_t nbin = octa_bin(nx, ny, nz, kp.nb_log2);
-  const uint64_t dbin = glossy ? octa_bin(ox, oy, oz, kp.db_log2) : 0ull;
-  key = ((uint64_t)lvl << 59) | ((uint64_t)glossy << 58) | (dbin << 52) | (nbin << 48) |
-        (iz << 32) | (iy << 16) | ix;
-  return true;
+  float fx, fy, fz;
+  const uint32_t ix = grid16(px, shift, fx), iy = grid16(py, shift, fy), iz = grid16(pz, shift, fz);
+  // a coordinate outside [-2^15, 2^15): an integer f with |f + 1/2| > 2^15 - 1/2
+  ovf = fmaxf(fmaxf(fabsf(fx + 0.5f), fabsf(fy + 0.5f)), fabsf(fz + 0.5f)) > 32767.5f;
+  uint32_t hi = ((uint32_t)lvl << 27) | (octa_bin(nx, ny, nz, kp.nb_log2) << 16) | iz;
+  if (has_rough) {
+    const bool glossy = rough < kp.rough_thr;
+    ok &= (int)__builtin_isfinite(rough) & ((int)!glossy | (int)finite3(ox, oy, oz));
+    if (__ballot(glossy)) hi |= glossy ? (1u << 26) | (octa_bin(ox, oy, oz, kp.db_log2) << 20) : 0u;
+  }
+  key = ((uint64_t)hi << 32) | (iy << 16) | ix;
+  return ok != 0;
 }
 
 // ------------------------------------------------------------------ state encodings
