@@ -198,8 +198,7 @@ typedef struct psf_config {
                                 (0 = default: 11, or 12 for tables of 2^25
                                 slots or more; else 8..12.  With
                                 PSF_FLAG_TRACK_VARIANCE or weighted = 1:
-                                default 10, or 11 for tables of 2^24
-                                slots or more; at most 11).  A table of
+                                default 11, at most 11).  A table of
                                 more than 16384 partitions takes the direct
                                 strategy. */
   uint64_t max_batch;        /* partitioned insert: records binned per launch

@@ -613,18 +613,16 @@ __global__ void __launch_bounds__(kShThreads) k_merge_sh(TableView tv, PartView 
   if (tid == 0) s_dropped = s_nlist = 0;
   __syncthreads();
 
-  RunReader<kShThreads / 64> rr(pv, p, P, ntiles);
-  rr.for_each_batch([&](const uint64_t* at, const bool* ev, uint32_t) {
+  constexpr uint32_t kEntryBatch = 4;  // entries per lane loaded before processing
+  const RunReader<kShThreads / 64> rr(pv, p, P, ntiles);
+  const RunChunk ch0 = rr.chunk_of(rr.w_lo);
+  rr.for_each_batch<kEntryBatch>(ch0, 0, [&](const uint32_t* at, const bool* ev) {
     unsigned long long ek[kEntryBatch];
-    float w[kEntryBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kEntryBatch; ++q) ek[q] = pv.stage_key[at[q]];
 #pragma unroll
     for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      ek[q] = pv.stage_key[at[q]];
-      w[q] = pv.weights ? pv.stage_v[at[q]].w : 1.0f;
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      if (!ev[q] || w[q] == 0.0f) continue;  // w = 0: a sample its weight rejects
+      if (!ev[q] || (ek[q] & kLookupOnlyBit)) continue;  // (a sample its weight rejects)
       const uint32_t start = (uint32_t)fmix64(ek[q]) & (B - 1);
       bool found = false;
       for (uint32_t i = 0; i < tv.max_probe && !found; ++i) {
@@ -656,7 +654,7 @@ __global__ void __launch_bounds__(kShThreads) k_merge_sh(TableView tv, PartView 
   for (uint32_t c0 = 0; c0 < n_touched; c0 += kShCells) {
     for (uint32_t i = tid; i < kShSums * kShCells; i += kShThreads) s_sum[i] = 0.0;
     __syncthreads();
-    rr.for_each_batch([&](const uint64_t* at, const bool* ev, uint32_t) {
+    rr.for_each_batch<kEntryBatch>(ch0, 0, [&](const uint32_t* at, const bool* ev) {
       unsigned long long ek[kEntryBatch];
       float4 v[kEntryBatch], nrm[kEntryBatch];
 #pragma unroll
@@ -667,7 +665,7 @@ __global__ void __launch_bounds__(kShThreads) k_merge_sh(TableView tv, PartView 
       }
 #pragma unroll
       for (uint32_t q = 0; q < kEntryBatch; ++q) {
-        if (!ev[q] || v[q].w == 0.0f) continue;
+        if (!ev[q] || (ek[q] & kLookupOnlyBit)) continue;
         const uint32_t start = (uint32_t)fmix64(ek[q]) & (B - 1);
         uint32_t c = kNone;
         for (uint32_t i = 0; i < tv.max_probe; ++i) {

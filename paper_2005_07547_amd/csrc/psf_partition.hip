@@ -15,14 +15,13 @@
 //            record's entry position in the tile);
 //   (transpose -- for large launches, the offset table turned so that a
 //            partition's offsets are one row);
-//   merge -- one block per partition (512 threads, or 1024 where the
-//            partition's LDS leaves room for one block per CU) loads the
-//            partition's keys into LDS, gathers that partition's entries
-//            from every tile, finds or claims each key's slot and
+//   merge -- one block per partition loads the partition's keys into LDS,
+//            gathers the keys of that partition's entries from every tile,
+//            finds or claims each one's slot, lists the touched slots, and
 //            accumulates count (u32) and sums (binary64; also the weights
 //            of a weighted table and the squared luminances of one that
-//            keeps the variance) with LDS atomics, lists the touched
-//            slots, then writes them back:
+//            keeps the variance) of the touched cells with LDS atomics,
+//            then writes them back:
 //            either adding into the global accumulators (plain insert) or,
 //            when the whole frame is in this launch, applying the temporal
 //            blend (Eq. 10-11) directly so the accumulators never touch HBM;
@@ -38,16 +37,6 @@
 
 namespace psf {
 
-// Threads and records per thread of the binning pass: a tile of 4096 records
-// takes 1024 threads with 4 records each (6144: 768 with 8, weighted 512
-// with 12; 8192: 1024 with 8).  The pass waits on one dependent step after
-// another (record loads, LDS ranks, scan, staging), so twice the wavefronts
-// with half the records each hide more of it: 70.6 -> 62.0 us for 3,686,400
-// records (900 tiles) against 512 threads with 8, 174 -> 163 us for 1688
-// tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
-// (one of 8192 records, by its LDS).
-constexpr int bin_waves(uint32_t threads, uint32_t per) { return threads * per > 6144 ? 4 : (int)threads / 128; }
-constexpr int kMergeThreads = 512;
 constexpr uint32_t kMaxPartLog2 = 12;
 
 bool bin_per_ok(uint32_t per) { return per == 8 || per == 12 || per == 16; }
@@ -145,6 +134,18 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
   return 63u - (uint32_t)__builtin_clzll(~cont & upto);
 }
 
+// Threads and records per thread of the binning pass: a tile of 4096 records
+// takes 1024 threads with 4 records each (6144: 768 with 8, weighted 512
+// with 12; 8192: 1024 with 8).  The pass waits on one dependent step after
+// another (record loads, LDS ranks, scan, staging), so twice the wavefronts
+// with half the records each hide more of it: 70.6 -> 62.0 us for 3,686,400
+// records (900 tiles) against 512 threads with 8, 174 -> 163 us for 1688
+// tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
+// (one of 8192 records, by its LDS; twelve weighted records a thread spill
+// at 128 registers).
+constexpr int bin_waves(uint32_t threads, uint32_t per, bool weights) {
+  return threads * per > 6144 ? 4 : per > 8 && weights ? 3 : (int)threads / 128;
+}
 template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
 __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const KeyParams& kp,
                                          const TableView& tv, const PartView& pv, uint32_t tile) {
@@ -257,6 +258,9 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
       const bool entry = kv && (sv || pv.perm);
       pos[j] = entry ? ((kv && sv) ? 0u : kPosLookupOnly) | ((ovf && sv) ? kPosOverflow : 0u) : ~0u;
     }
+    // (the next batch's loads stay behind this one's keys: hoisted, they
+    // spill)
+    __builtin_amdgcn_sched_barrier(0);
   }
   // entries per partition (ranks), after merging runs of one cell in
   // neighbouring lanes: only a run's head gets an entry
@@ -392,15 +396,15 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   if (kW) {
     // The weights are first read here.  A sample whose weight is not finite
     // and > 0 is rejected: counted as skipped (not as a coordinate
-    // overflow) and staged with n = 0, so the merge pass only looks it up
-    // (with the fused query) or ignores it; an accepted one is staged as
+    // overflow) and staged for lookup only, so the merge pass only looks it
+    // up (with the fused query) or ignores it; an accepted one is staged as
     // w (r, g, b) with n = w.
 #pragma unroll
     for (uint32_t j = 0; j < kPer; ++j) {
       wn[j] = 0.0f;
       if (!own_entry(j)) continue;
       const float w = rec.weight[t0 + (uint64_t)j * kThreads + tid];
-      if (pos[j] & kPosLookupOnly) continue;
+      if (key[j] & kLookupOnlyBit) continue;
       if (__builtin_isfinite(w) && w > 0.0f) {
         if (!kN) {  // (the SH sums weight the sample themselves, in binary64)
           rgb[j][0] *= w;
@@ -409,6 +413,7 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
         }
         wn[j] = w;
       } else {
+        key[j] |= kLookupOnlyBit;
         ++n_skip;
         n_ovf -= (pos[j] & kPosOverflow) ? 1u : 0u;
       }
@@ -450,7 +455,7 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
 }
 
 template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer))))
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer, kX & kXWeight))))
 k_bin(RecPtrs rec, uint64_t n, KeyParams kp, TableView tv, PartView pv) {
   bin_body<kThreads, kPer, kX>(rec, n, kp, tv, pv, blockIdx.x);
 }
@@ -484,28 +489,51 @@ __global__ void __launch_bounds__(kTransposeThreads) k_transpose_runs(PartView p
 }
 
 // ------------------------------------------------------------------ merge
-// Batches per wave whose (entry, slot) pairs stay in registers for the
-// fused query; a wave with more batches finds the later entries' slots again.
-constexpr uint32_t kKeepBatches = 2;
-constexpr uint32_t kLookupLater = 0xfffffffeu;  // kept slot of a lookup-only entry
+// LDS of a merge block: the partition's keys and, per slot, its place in the
+// list of touched slots (16-bit; 10 bytes a slot), then sums for `cells`
+// touched cells (30 bytes each: three binary64 sums, a count and the slot's
+// number; 38 with a further sum per cell).  A frame touches about one slot in
+// eight, so sums for 5/16 of the slots (1/4 with the further sum) do in one
+// round, in half the LDS that sums for every slot would take: a CU holds 24
+// wavefronts (two blocks of 4096 slots, four of 2048, eight of 1024) instead
+// of 16, in separate blocks that are not all in the same phase.  3,686,400
+// records into 2^22 slots: 98 -> 82 us; 10,368,000 into 2^24: 336 -> 278 us.
+// (32 wavefronts need 64 registers and spill 37 more: 176 us.)  A partition
+// with more touched cells takes further rounds over its entries.
+__host__ __device__ constexpr uint32_t merge_cells(uint32_t slots, bool extra) {
+  return extra ? slots / 4 : slots / 16 * 5;
+}
+__host__ __device__ constexpr size_t merge_lds_bytes(uint32_t slots, bool extra) {
+  return (size_t)slots * (8 + 2) + (size_t)merge_cells(slots, extra) * (24 + 4 + 2 + (extra ? 8 : 0));
+}
+
+// Entries per lane of a wave's first batch, held in registers to the end, and
+// of the batches after it, which each step reads again.
+constexpr uint32_t kEntryBatch = 4, kLaterBatch = 2;
+
+// What became of an entry's key: a slot number (with the probes it took, at
+// most 15, from kProbesShift on), a key that found no slot, or an entry
+// staged for lookup only.
+constexpr uint32_t kProbesShift = 16, kSlotBits = 0xffffu;
+constexpr uint32_t kDropped = 0xffffffffu, kLookupLater = 0xfffffffeu, kAbsent = 0xfffffffdu;
 
 // One partition: blk is the block's index among the partition blocks of this
 // table (the XCD-aware order maps it to a partition).  With results (fused
 // mode only), every staged entry of the partition is overwritten with the
 // value its cell holds after the blend (kDroppedBits in place of red when
 // its key found no slot).
-template <bool kFused, int kThreads = kMergeThreads>
+template <bool kFused, int kThreads, bool kVar>
 __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& pv, uint32_t ntiles,
                                            const BlendParams& bp, uint32_t blk, bool results) {
-  // key[B] | cnt[B] | sum[3][B] (binary64: LDS f64 atomics are both faster
-  // than f32 ones on gfx950 and exact enough to make the sum order
-  // immaterial), then, in a table that keeps the luminance variance or has
-  // weighted counters, sumx[B]: the squared luminances (staged per entry),
-  // or the weights (binary64 like the value sums, rounded once to binary32
-  // at the write-back, so the counters do not depend on the order of the
-  // atomics; cnt then only marks the slots touched; every entry is one
-  // record).  After the blend the sums hold the cells' new values.
-  // Last, list[B] (16-bit): the touched slots, gathered for the write-back.
+  // key[B] | sum[3][N] (binary64: LDS f64 atomics are both faster than f32
+  // ones on gfx950 and exact enough to make the sum order immaterial), then,
+  // in a table that keeps the luminance variance or has weighted counters,
+  // sumx[N]: the squared luminances (staged per entry), or the weights
+  // (binary64 like the value sums, rounded once to binary32 at the
+  // write-back, so the counters do not depend on the order of the atomics;
+  // cnt is then unused; every entry is one record) | cnt[N] | place of a
+  // slot in the list of touched slots[B] (16-bit) | the round's part of that
+  // list[N] (16-bit).  After the blend the sums hold the cells' new values.
   extern __shared__ unsigned long long s_dyn[];
   __shared__ uint32_t s_dropped, s_nlist, s_sat;
   __shared__ uint32_t s_hist[16];
@@ -517,22 +545,22 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   const uint64_t base = (uint64_t)p << tv.part_log2;
   const bool stats = (tv.flags & 1u) != 0;
   const bool wtd = weighted(tv);
+  const uint32_t N = merge_cells(B, kVar || wtd);
   unsigned long long* s_key = s_dyn;
-  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_key + B);
-  double* s_sum0 = reinterpret_cast<double*>(s_cnt + B);  // B >= 256: 8-byte aligned
-  double* s_sum1 = s_sum0 + B;
-  double* s_sum2 = s_sum1 + B;
-  double* s_sumx = s_sum2 + B;  // only with tv.var or wtd
-  const bool var = tv.var != nullptr;
-  // the touched slots' indices (B entries), after the sums
-  uint16_t* s_list = reinterpret_cast<uint16_t*>(s_sumx + ((var || wtd) ? B : 0u));
+  double* s_sum0 = reinterpret_cast<double*>(s_key + B);
+  double* s_sum1 = s_sum0 + N;
+  double* s_sum2 = s_sum1 + N;
+  double* s_sumx = s_sum2 + N;  // only with tv.var or wtd
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_sumx + ((kVar || wtd) ? N : 0u));
+  uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_cnt + N);
+  uint16_t* s_list = s_idx + B;
+  constexpr uint32_t kNone = 0xffffu;
   if (!kFused) results = false;
 
-  RunReader<kWaves> rr(pv, p, P, ntiles);
-
-  // keys first, then the first runs, then the wave's first batch of entries:
-  // all in flight together, before the key table is built
-  constexpr uint32_t kKeysPerThread = (1u << kMaxPartLog2) / kThreads;
+  // keys first, then the first runs, then the keys of the wave's first batch
+  // of entries: all in flight together, before the key table is built
+  const RunReader<kWaves> rr(pv, p, P, ntiles);
+  constexpr uint32_t kKeysPerThread = 6;  // (the launch has at least B / 6 threads)
   unsigned long long kk[kKeysPerThread];
 #pragma unroll
   for (uint32_t j = 0; j < kKeysPerThread; ++j) {
@@ -540,270 +568,287 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     kk[j] = s < B ? tv.keys[base + s] : kEmpty;
   }
   RunChunk ch0{};
-  uint64_t at0[kEntryBatch];
-  bool ev0[kEntryBatch];
+  uint32_t at0[kEntryBatch], code0[kEntryBatch];
   unsigned long long ek0[kEntryBatch];
-  float4 v0[kEntryBatch];
-  float q0[kEntryBatch];  // variance tables: the entries' squared-luminance sums
-  if (rr.w_lo < rr.w_hi) {
-    ch0 = rr.chunk_of(rr.w_lo);
-    rr.batch_of(ch0, 0, at0, ev0);
+  bool ev0[kEntryBatch];
 #pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      ek0[q] = pv.stage_key[at0[q]];
-      v0[q] = pv.stage_v[at0[q]];
-      q0[q] = var ? pv.stage_q[at0[q]] : 0.0f;
-    }
+  for (uint32_t q = 0; q < kEntryBatch; ++q) ev0[q] = false;
+  const bool any = rr.w_lo < rr.w_hi;  // the wave has tiles (wave-uniform)
+  if (any) {
+    ch0 = rr.chunk_of(rr.w_lo);
+    rr.template batch_of<kEntryBatch>(ch0, 0, at0, ev0);
+#pragma unroll
+    for (uint32_t q = 0; q < kEntryBatch; ++q) ek0[q] = pv.stage_key[at0[q]];
   }
+  auto clear_sums = [&]() {
+    for (uint32_t c = tid; c < N; c += kThreads) {
+      s_sum0[c] = s_sum1[c] = s_sum2[c] = 0.0;
+      if (kVar || wtd) s_sumx[c] = 0.0;
+      s_cnt[c] = 0;
+    }
+  };
+  clear_sums();
 #pragma unroll
   for (uint32_t j = 0; j < kKeysPerThread; ++j) {
     const uint32_t s = tid + j * kThreads;
     if (s < B) {
       s_key[s] = kk[j];
-      s_cnt[s] = 0;
-      s_sum0[s] = s_sum1[s] = s_sum2[s] = 0.0;
-      if (var || wtd) s_sumx[s] = 0.0;
+      s_idx[s] = (uint16_t)kNone;
     }
   }
   if (tid == 0) s_dropped = s_nlist = s_sat = 0;
   if (tid < 16) s_hist[tid] = 0;
   __syncthreads();
 
-  // (staging index, slot) of the lane's entries of the first kKeepBatches
-  // batches; ~0u marks an absent entry (index) or a dropped key (slot)
-  uint32_t keep_at[kKeepBatches][kEntryBatch], keep_slot[kKeepBatches][kEntryBatch];
+  // Finds the slot of a sample's key, or claims one, and marks it touched.
+  auto claim = [&](unsigned long long key) {
+    const uint32_t start = (uint32_t)fmix64(key) & (B - 1);
+    for (uint32_t i = 0; i < tv.max_probe; ++i) {
+      const uint32_t s = (start + i) & (B - 1);
+      unsigned long long cur = s_key[s];
+      if (cur == kEmpty) cur = atomicCAS(&s_key[s], kEmpty, key);
+      if (cur == kEmpty || cur == key) {
+        s_idx[s] = 0;
+        return s | ((i < 15 ? i : 15u) << kProbesShift);
+      }
+    }
+    return kDropped;
+  };
+  // The same once every key has its slot (also of a lookup-only entry).
+  auto find = [&](unsigned long long key) {
+    const uint32_t start = (uint32_t)fmix64(key) & (B - 1);
+    for (uint32_t i = 0; i < tv.max_probe; ++i) {
+      const uint32_t s = (start + i) & (B - 1);
+      const unsigned long long cur = s_key[s];
+      if (cur == key) return s | ((i < 15 ? i : 15u) << kProbesShift);
+      if (cur == kEmpty) break;
+    }
+    return kDropped;
+  };
 #pragma unroll
-  for (uint32_t b = 0; b < kKeepBatches; ++b)
-#pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) keep_at[b][q] = keep_slot[b][q] = ~0u;
-
-  auto accumulate = [&](const uint64_t* at, const bool* ev, const unsigned long long* ek, const float4* v,
-                        const float* qv, uint32_t nb) {
+  for (uint32_t q = 0; q < kEntryBatch; ++q)
+    code0[q] = !ev0[q] ? kAbsent : (ek0[q] & kLookupOnlyBit) ? kLookupLater : claim(ek0[q]);
+  // the first batch's values arrive while the touched slots are listed
+  float4 v0[kEntryBatch];
+  float q0[kEntryBatch];  // variance tables: the entries' squared-luminance sums
+  if (any) {
 #pragma unroll
     for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      uint32_t slot = ~0u;
-      // n = 0: an entry staged for lookup only (a rejected sample); with the
-      // fused query it is looked up after the blend, else it is ignored
-      if (results && v[q].w == 0.0f) slot = kLookupLater;
-      if (ev[q] && v[q].w != 0.0f) {
-        // records behind the entry, for the drop and probe statistics
-        const uint32_t recs = pv.weights ? 1u : (uint32_t)v[q].w;
-        const unsigned long long key = ek[q];
-        const uint32_t start = (uint32_t)fmix64(key) & (B - 1);
-        uint32_t i = 0;
-        for (; i < tv.max_probe; ++i) {
-          const uint32_t s = (start + i) & (B - 1);
-          unsigned long long cur = s_key[s];
-          if (cur == kEmpty) cur = atomicCAS(&s_key[s], kEmpty, key);
-          if (cur == kEmpty || cur == key) {
-            slot = s;
-            break;
-          }
-        }
-        if (slot == ~0u) {
-          atomicAdd(&s_dropped, recs);
-        } else {
-          if (stats) atomicAdd(&s_hist[i < 15 ? i : 15], recs);
-          if (wtd) {
-            atomicAdd(&s_sumx[slot], (double)v[q].w);
-            s_cnt[slot] = 1u;
-          } else {
-            atomicAdd(&s_cnt[slot], (uint32_t)v[q].w);
-          }
-          atomicAdd(&s_sum0[slot], (double)v[q].x);
-          atomicAdd(&s_sum1[slot], (double)v[q].y);
-          atomicAdd(&s_sum2[slot], (double)v[q].z);
-          if (var) atomicAdd(&s_sumx[slot], (double)qv[q]);
-        }
-      }
-      if (results) {
-        const uint32_t a = ev[q] ? (uint32_t)at[q] : ~0u;
-#pragma unroll
-        for (uint32_t b = 0; b < kKeepBatches; ++b) {
-          if (nb == b) {
-            keep_at[b][q] = a;
-            keep_slot[b][q] = slot;
-          }
-        }
-      }
-    }
-  };
-  // the first batch was loaded above; every later one into the same registers
-  uint32_t batches = 0;
-  for (uint32_t c0 = rr.w_lo; c0 < rr.w_hi; c0 += 64 * kRunsPerLane) {
-    const RunChunk ch = c0 == rr.w_lo ? ch0 : rr.chunk_of(c0);
-    for (uint32_t e0 = 0; e0 < ch.total; e0 += 64 * kEntryBatch, ++batches) {
-      if (c0 != rr.w_lo || e0 != 0) {
-        rr.batch_of(ch, e0, at0, ev0);
-#pragma unroll
-        for (uint32_t q = 0; q < kEntryBatch; ++q) {
-          ek0[q] = pv.stage_key[at0[q]];
-          v0[q] = pv.stage_v[at0[q]];
-          q0[q] = var ? pv.stage_q[at0[q]] : 0.0f;
-        }
-      }
-      accumulate(at0, ev0, ek0, v0, q0, batches);
+      v0[q] = pv.stage_v[at0[q]];
+      q0[q] = kVar ? pv.stage_q[at0[q]] : 0.0f;
     }
   }
+  rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch, [&](const uint32_t* at, const bool* ev) {
+    unsigned long long ek[kLaterBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q) ek[q] = pv.stage_key[at[q]];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q)
+      if (ev[q] && !(ek[q] & kLookupOnlyBit)) claim(ek[q]);
+  });
   __syncthreads();
 
-  // List the touched slots (about one in eight, scattered), so that the
-  // write-back runs on full waves: each thread then blends at most kWb
-  // cells, whose old slots are loaded together (one memory round trip).
+  // List the touched slots (about one in eight, scattered), so that the sums
+  // are kept for them alone and the write-back runs on full waves.
   for (uint32_t s0 = 0; s0 < B; s0 += kThreads) {
     const uint32_t s = s0 + tid;
-    const bool hit = s < B && s_cnt[s] != 0u;
+    const bool hit = s < B && s_idx[s] != kNone;
     const unsigned long long m = __ballot(hit);
     uint32_t at = 0;
     if (lane == 0 && m) at = atomicAdd(&s_nlist, (uint32_t)__popcll(m));
     at = (uint32_t)__shfl((int)at, 0);
-    if (hit)
-      s_list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-          (uint16_t)s;
+    if (hit) {
+      at += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      s_idx[s] = (uint16_t)at;
+      if (at < N) s_list[at] = (uint16_t)s;
+    }
   }
   __syncthreads();
   const uint32_t n_touched = s_nlist;
   bool sat = false;
-  constexpr uint32_t kWb = 2;
-  for (uint32_t i0 = 0; i0 < n_touched; i0 += kWb * kThreads) {
-    uint32_t sl[kWb];
-    Slot old[kWb];
-    Acc acc_old[kWb];
-    float var_old[kWb];  // fused: the variance
-    double q_old[kWb];   // not fused: the pending squared-luminance sum
-#pragma unroll
-    for (uint32_t j = 0; j < kWb; ++j) {
-      const uint32_t i = i0 + j * kThreads + tid;
-      sl[j] = i < n_touched ? (uint32_t)s_list[i] : ~0u;
+
+  // Adds an entry to its cell's sums if the cell is in the round from c0 on.
+  auto add = [&](uint32_t code, const float4& v, float qv, uint32_t c0) {
+    const uint32_t recs = pv.weights ? 1u : (uint32_t)v.w;  // records behind the entry
+    if (code == kDropped) {
+      if (c0 == 0) atomicAdd(&s_dropped, recs);
+      return;
     }
-    // absent entries read the partition's first slot, so that the group's
-    // loads carry no branches and overlap
+    const uint32_t c = (uint32_t)s_idx[code & kSlotBits] - c0;
+    if (c >= N) return;
+    if (stats) atomicAdd(&s_hist[code >> kProbesShift], recs);
+    if (wtd)
+      atomicAdd(&s_sumx[c], (double)v.w);
+    else
+      atomicAdd(&s_cnt[c], (uint32_t)v.w);
+    atomicAdd(&s_sum0[c], (double)v.x);
+    atomicAdd(&s_sum1[c], (double)v.y);
+    atomicAdd(&s_sum2[c], (double)v.z);
+    if (kVar) atomicAdd(&s_sumx[c], (double)qv);
+  };
+  auto add_batch = [&](const uint32_t* at, const bool* ev, uint32_t c0) {
+    unsigned long long ek[kLaterBatch];
+    float4 v[kLaterBatch];
+    float qv[kLaterBatch];
 #pragma unroll
-    for (uint32_t j = 0; j < kWb; ++j) {
-      const uint64_t src = base + (sl[j] != ~0u ? sl[j] : 0u);
-      old[j] = tv.slots[src];
-      if (!kFused) acc_old[j] = tv.acc[src];
-      if (var) {
-        if (kFused)
-          var_old[j] = tv.var[src];
-        else
-          q_old[j] = tv.acc_q[src];
+    for (uint32_t q = 0; q < kLaterBatch; ++q) {
+      ek[q] = pv.stage_key[at[q]];
+      v[q] = pv.stage_v[at[q]];
+      qv[q] = kVar ? pv.stage_q[at[q]] : 0.0f;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q)
+      if (ev[q] && !(ek[q] & kLookupOnlyBit)) add(find(ek[q]), v[q], qv[q], c0);
+  };
+  // What the table holds of a touched slot before this launch.
+  struct Old {
+    Slot slot;
+    Acc acc;    // not fused
+    float v;    // fused: the variance
+    double q;   // not fused: the pending squared-luminance sum
+  };
+  auto load_old = [&](uint64_t g) {
+    Old o;
+    o.slot = tv.slots[g];
+    if (!kFused) o.acc = tv.acc[g];
+    if (kVar) {
+      if (kFused)
+        o.v = tv.var[g];
+      else
+        o.q = tv.acc_q[g];
+    }
+    return o;
+  };
+  // Writes touched cell c of the round back (slot s of the partition).
+  auto write_back = [&](uint32_t c, uint32_t s, const Old& old) {
+    const uint64_t g = base + s;
+    // the frame's counter word (a weighted table's weight sum rounds once)
+    const uint32_t cn = wtd ? __float_as_uint((float)s_sumx[c]) : s_cnt[c];
+    const unsigned long long k = s_key[s];
+    if (kFused) {
+      const float alpha = blend_alpha(bp, cn, old.slot.c_old, wtd);
+      float L[3];
+      load_blend_state(old.slot, bp.dtype, L[0], L[1], L[2]);
+      // the new sample mean, rounded once from binary64
+      const double cd = wtd ? (double)__uint_as_float(cn) : (double)cn;
+      const float means[3] = {(float)(s_sum0[c] / cd), (float)(s_sum1[c] / cd), (float)(s_sum2[c] / cd)};
+      float out[3];
+      for (int ch = 0; ch < 3; ++ch) {
+        const float m = means[ch];
+        out[ch] = alpha == 1.0f ? m : (1.0f - alpha) * L[ch] + alpha * m;
+      }
+      if (kVar) {
+        double m, s2;
+        frame_moments(s_sum0[c], s_sum1[c], s_sum2[c], s_sumx[c], cd, m, s2);
+        tv.var[g] = blend_variance(old.v, alpha, luma32(L[0], L[1], L[2]), m, s2);
+      }
+      uint32_t enc[4], pad;
+      encode_state(bp.dtype, out[0], out[1], out[2], enc, pad, sat);
+      Slot nw;
+      nw.key = k;
+      nw.c_old = counter_add(old.slot.c_old, cn, wtd);
+      nw.pad = pad;
+      nw.L[0] = enc[0];
+      nw.L[1] = enc[1];
+      nw.L[2] = enc[2];
+      nw.L[3] = enc[3];
+      tv.slots[g] = nw;
+      if (old.slot.key != k) tv.keys[g] = k;
+      if (results) {
+        // what a lookup of the cell returns from now on
+        float v[3];
+        load_state(nw, bp.dtype, v[0], v[1], v[2]);
+        s_sum0[c] = v[0];
+        s_sum1[c] = v[1];
+        s_sum2[c] = v[2];
+      }
+    } else {
+      Acc a = old.acc;
+      a.n = counter_add(a.n, cn, wtd);
+      a.s[0] += (float)s_sum0[c];
+      a.s[1] += (float)s_sum1[c];
+      a.s[2] += (float)s_sum2[c];
+      tv.acc[g] = a;
+      if (kVar) tv.acc_q[g] = old.q + s_sumx[c];
+      if (old.slot.key != k) {
+        tv.slots[g].key = k;
+        tv.keys[g] = k;
       }
     }
+  };
+  // The value a lookup of the entry's cell returns (kDroppedBits if none),
+  // written over the entry in one 16-byte store; in the round of its cell.
+  auto answer = [&](uint32_t at, uint32_t code, uint32_t c0) {
+    if (code == kLookupLater) code = find(pv.stage_key[at] & ~kLookupOnlyBit);
+    const uint32_t i = code == kDropped ? kNone : (uint32_t)s_idx[code & kSlotBits];
+    if (i != kNone ? i - c0 >= N : c0 != 0) return;
+    float v[3] = {__uint_as_float(kDroppedBits), 0.0f, 0.0f};
+    if (i != kNone) {
+      v[0] = (float)s_sum0[i - c0];
+      v[1] = (float)s_sum1[i - c0];
+      v[2] = (float)s_sum2[i - c0];
+    } else if (code != kDropped) {
+      // a lookup-only entry whose cell this launch did not touch
+      const Slot sl = tv.slots[base + (code & kSlotBits)];
+      if (sl.c_old > 0) load_state(sl, bp.dtype, v[0], v[1], v[2]);
+    }
+    pv.stage_v[at] = make_float4(v[0], v[1], v[2], 0.0f);
+  };
+  auto answer_batch = [&](const uint32_t* at, const bool* ev, uint32_t c0) {
+    unsigned long long ek[kLaterBatch];
 #pragma unroll
-    for (uint32_t j = 0; j < kWb; ++j) {
-      if (sl[j] == ~0u) continue;
-      const uint32_t s = sl[j];
-      const uint64_t g = base + s;
-      // the frame's counter word (a weighted table's weight sum rounds once)
-      const uint32_t c = wtd ? __float_as_uint((float)s_sumx[s]) : s_cnt[s];
-      const unsigned long long k = s_key[s];
-      if (kFused) {
-        const float alpha = blend_alpha(bp, c, old[j].c_old, wtd);
-        float L[3];
-        load_blend_state(old[j], bp.dtype, L[0], L[1], L[2]);
-        // the new sample mean, rounded once from binary64
-        const double cd = wtd ? (double)__uint_as_float(c) : (double)c;
-        const float means[3] = {(float)(s_sum0[s] / cd), (float)(s_sum1[s] / cd), (float)(s_sum2[s] / cd)};
-        float out[3];
-        for (int ch = 0; ch < 3; ++ch) {
-          const float m = means[ch];
-          out[ch] = alpha == 1.0f ? m : (1.0f - alpha) * L[ch] + alpha * m;
-        }
-        if (var) {
-          double m, s2;
-          frame_moments(s_sum0[s], s_sum1[s], s_sum2[s], s_sumx[s], cd, m, s2);
-          tv.var[g] = blend_variance(var_old[j], alpha, luma32(L[0], L[1], L[2]), m, s2);
-        }
-        uint32_t enc[4], pad;
-        encode_state(bp.dtype, out[0], out[1], out[2], enc, pad, sat);
-        Slot nw;
-        nw.key = k;
-        nw.c_old = counter_add(old[j].c_old, c, wtd);
-        nw.pad = pad;
-        nw.L[0] = enc[0];
-        nw.L[1] = enc[1];
-        nw.L[2] = enc[2];
-        nw.L[3] = enc[3];
-        tv.slots[g] = nw;
-        if (old[j].key != k) tv.keys[g] = k;
-        if (results) {
-          // what a lookup of the cell returns from now on
-          float v[3];
-          load_state(nw, bp.dtype, v[0], v[1], v[2]);
-          s_sum0[s] = v[0];
-          s_sum1[s] = v[1];
-          s_sum2[s] = v[2];
-        }
-      } else {
-        Acc a = acc_old[j];
-        a.n = counter_add(a.n, c, wtd);
-        a.s[0] += (float)s_sum0[s];
-        a.s[1] += (float)s_sum1[s];
-        a.s[2] += (float)s_sum2[s];
-        tv.acc[g] = a;
-        if (var) tv.acc_q[g] = q_old[j] + s_sumx[s];
-        if (old[j].key != k) {
-          tv.slots[g].key = k;
-          tv.keys[g] = k;
-        }
-      }
+    for (uint32_t q = 0; q < kLaterBatch; ++q) ek[q] = pv.stage_key[at[q]];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q)
+      if (ev[q]) answer(at[q], find(ek[q] & ~kLookupOnlyBit), c0);
+  };
+
+  // The first round (the only one unless the partition is dense), with the
+  // first batch in registers and the thread's first cell's old slot on its
+  // way while the entries are summed.
+  const uint32_t cells0 = n_touched < N ? n_touched : N;
+  const uint32_t sl0 = tid < cells0 ? (uint32_t)s_list[tid] : 0u;
+  const Old old0 = load_old(base + sl0);
+#pragma unroll
+  for (uint32_t q = 0; q < kEntryBatch; ++q)
+    if (code0[q] != kAbsent && code0[q] != kLookupLater) add(code0[q], v0[q], q0[q], 0);
+  rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch,
+                                          [&](const uint32_t* at, const bool* ev) { add_batch(at, ev, 0); });
+  __syncthreads();
+  if (tid < cells0) write_back(tid, sl0, old0);
+  for (uint32_t c = tid + kThreads; c < cells0; c += kThreads) write_back(c, s_list[c], load_old(base + s_list[c]));
+  if (results) {
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kEntryBatch; ++q)
+      if (code0[q] != kAbsent) answer(at0[q], code0[q], 0);
+    rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch,
+                                            [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, 0); });
+  }
+  // Further rounds read the entries again (each keeps its value until the
+  // round that answers it).
+  for (uint32_t c0 = N; c0 < n_touched; c0 += N) {
+    __syncthreads();
+    clear_sums();
+    for (uint32_t s = tid; s < B; s += kThreads) {
+      const uint32_t i = (uint32_t)s_idx[s] - c0;
+      if (s_idx[s] != kNone && i < N) s_list[i] = (uint16_t)s;
+    }
+    __syncthreads();
+    rr.template for_each_batch<kLaterBatch>(ch0, 0,
+                                            [&](const uint32_t* at, const bool* ev) { add_batch(at, ev, c0); });
+    __syncthreads();
+    const uint32_t cells = n_touched - c0 < N ? n_touched - c0 : N;
+    for (uint32_t c = tid; c < cells; c += kThreads) write_back(c, s_list[c], load_old(base + s_list[c]));
+    if (results) {
+      __syncthreads();
+      rr.template for_each_batch<kLaterBatch>(ch0, 0,
+                                              [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, c0); });
     }
   }
+
   if (kFused && sat) atomicAdd(&s_sat, 1u);
   __syncthreads();
-
-  if (results) {
-    // slot of a key in the final LDS key table, or ~0u
-    auto find = [&](unsigned long long key) {
-      const uint32_t start = (uint32_t)fmix64(key) & (B - 1);
-      for (uint32_t i = 0; i < tv.max_probe; ++i) {
-        const uint32_t s = (start + i) & (B - 1);
-        const unsigned long long cur = s_key[s];
-        if (cur == key) return s;
-        if (cur == kEmpty) break;
-      }
-      return ~0u;
-    };
-    // the value a lookup of the cell in slot returns (kDroppedBits if none),
-    // written over the entry in one 16-byte store
-    auto put = [&](uint64_t at, uint32_t slot) {
-      float v[3] = {__uint_as_float(kDroppedBits), 0.0f, 0.0f};
-      if (slot != ~0u && s_cnt[slot] > 0) {
-        v[0] = (float)s_sum0[slot];
-        v[1] = (float)s_sum1[slot];
-        v[2] = (float)s_sum2[slot];
-      } else if (slot != ~0u) {
-        // a lookup-only entry whose cell this launch did not touch
-        const Slot sl = tv.slots[base + slot];
-        if (sl.c_old > 0) load_state(sl, bp.dtype, v[0], v[1], v[2]);
-      }
-      pv.stage_v[at] = make_float4(v[0], v[1], v[2], 0.0f);
-    };
-#pragma unroll
-    for (uint32_t b = 0; b < kKeepBatches; ++b) {
-#pragma unroll
-      for (uint32_t q = 0; q < kEntryBatch; ++q) {
-        if (keep_at[b][q] == ~0u) continue;
-        uint32_t slot = keep_slot[b][q];
-        if (slot == kLookupLater) slot = find(pv.stage_key[keep_at[b][q]] & ~kLookupOnlyBit);
-        put(keep_at[b][q], slot);
-      }
-    }
-    if (batches > kKeepBatches) {
-      // later batches: read the keys again and find their (final) slots
-      rr.for_each_batch([&](const uint64_t* at, const bool* ev, uint32_t nb) {
-        if (nb < kKeepBatches) return;
-        unsigned long long ek[kEntryBatch];
-#pragma unroll
-        for (uint32_t q = 0; q < kEntryBatch; ++q) ek[q] = pv.stage_key[at[q]];
-#pragma unroll
-        for (uint32_t q = 0; q < kEntryBatch; ++q)
-          if (ev[q]) put(at[q], find(ek[q] & ~kLookupOnlyBit));
-      });
-    }
-  }
-
   if (tid == 0) {
     if (s_dropped) atomicAdd(&tv.stats->dropped, (unsigned long long)s_dropped);
     if (kFused) {
@@ -817,13 +862,15 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     atomicAdd(&tv.stats->probe_hist[tid], (unsigned long long)s_hist[tid]);
 }
 
-// 512 threads per partition block, 1024 where the partition's LDS allows
-// one block per CU (4096 slots, or 2048 with a fifth sum per slot): 16
-// waves per CU either way.
-template <bool kFused, int kThreads>
-__global__ void __launch_bounds__(kThreads) k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp,
-                                                    int32_t results) {
-  merge_body<kFused, kThreads>(tv, pv, ntiles, bp, blockIdx.x, results != 0);
+// Threads of a merge block (768 for 4096 slots): the LDS of merge_lds_bytes
+// leaves room for 24 such wavefronts on a CU, at 80 registers (a table that
+// keeps the variance holds one more value an entry: 20 at 96).
+static uint32_t merge_threads(uint32_t part_log2) { return part_log2 >= 12 ? 768u : part_log2 == 11 ? 384u : 192u; }
+
+template <bool kFused, int kThreads, bool kVar>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kVar ? 5 : 6)))
+k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp, int32_t results) {
+  merge_body<kFused, kThreads, kVar>(tv, pv, ntiles, bp, blockIdx.x, results != 0);
 }
 
 // ------------------------------------------------------------------ unstage
@@ -910,12 +957,8 @@ static size_t bin_lds(uint32_t P, uint32_t tile) {
   return hist > stage ? hist : stage;
 }
 
-// A merge block whose LDS leaves room for no second block on a CU (160 KB)
-// takes 1024 threads, so that the CU still runs 16 waves.
-static bool merge_wide(size_t lds) { return lds > 80 * 1024; }
-
 static size_t merge_lds(const TableView& tv) {
-  return (size_t)(1u << tv.part_log2) * (8 + 4 + 24 + ((tv.var || weighted(tv)) ? 8 : 0) + 2);
+  return merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv));
 }
 
 bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n) {
@@ -974,33 +1017,40 @@ hipError_t launch_bin(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const
   return launch_bin_x<1024, 8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
 }
 
+template <bool kFused, int kThreads, bool kVar>
+static hipError_t launch_merge_t(const TableView& tv, const PartView& pv, uint32_t ntiles, const BlendParams& bp,
+                                 int32_t results, hipStream_t s) {
+  static LdsLimit lim;  // one per instantiation
+  const size_t shm = merge_lds(tv);
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge<kFused, kThreads, kVar>), shm, &lim);
+  if (e != hipSuccess) return e;
+  k_merge<kFused, kThreads, kVar><<<1u << (tv.log2_slots - tv.part_log2), kThreads, shm, s>>>(tv, pv, ntiles, bp, results);
+  return hipGetLastError();
+}
+
+template <bool kFused, bool kVar>
+static hipError_t launch_merge_f(const TableView& tv, const PartView& pv, uint32_t ntiles, const BlendParams& bp,
+                                 int32_t results, hipStream_t s) {
+  switch (merge_threads(tv.part_log2)) {
+    case 768: return launch_merge_t<kFused, 768, kVar>(tv, pv, ntiles, bp, results, s);
+    case 384: return launch_merge_t<kFused, 384, kVar>(tv, pv, ntiles, bp, results, s);
+    default: return launch_merge_t<kFused, 192, kVar>(tv, pv, ntiles, bp, results, s);
+  }
+}
+
 hipError_t launch_merge(uint64_t n, const TableView& tv, const PartView& pv, const BlendParams* fuse,
                         bool results, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (!partition_ok(tv, pv, n)) return hipErrorInvalidValue;
-  const uint32_t P = 1u << (tv.log2_slots - tv.part_log2);
   const uint32_t ntiles = (uint32_t)((n + pv.tile - 1) / pv.tile);
-  const size_t shm = merge_lds(tv);
   // staged lookup-only entries exist exactly when the bin pass wrote perm
   if (results != (pv.perm != nullptr) || (results && !fuse)) return hipErrorInvalidValue;
-  static LdsLimit lim[4];
-  const bool wide = merge_wide(shm);
-  const void* fn = fuse ? (wide ? reinterpret_cast<const void*>(&k_merge<true, 1024>)
-                                : reinterpret_cast<const void*>(&k_merge<true, kMergeThreads>))
-                        : (wide ? reinterpret_cast<const void*>(&k_merge<false, 1024>)
-                                : reinterpret_cast<const void*>(&k_merge<false, kMergeThreads>));
-  hipError_t e = lds_limit(fn, shm, &lim[(fuse ? 2 : 0) + (wide ? 1 : 0)]);
-  if (e != hipSuccess) return e;
   const int32_t res = results ? 1 : 0;
-  if (fuse && wide)
-    k_merge<true, 1024><<<P, 1024, shm, s>>>(tv, pv, ntiles, *fuse, res);
-  else if (fuse)
-    k_merge<true, kMergeThreads><<<P, kMergeThreads, shm, s>>>(tv, pv, ntiles, *fuse, res);
-  else if (wide)
-    k_merge<false, 1024><<<P, 1024, shm, s>>>(tv, pv, ntiles, BlendParams{}, 0);
-  else
-    k_merge<false, kMergeThreads><<<P, kMergeThreads, shm, s>>>(tv, pv, ntiles, BlendParams{}, 0);
-  return hipGetLastError();
+  if (tv.var)
+    return fuse ? launch_merge_f<true, true>(tv, pv, ntiles, *fuse, res, s)
+                : launch_merge_f<false, true>(tv, pv, ntiles, BlendParams{}, 0, s);
+  return fuse ? launch_merge_f<true, false>(tv, pv, ntiles, *fuse, res, s)
+              : launch_merge_f<false, false>(tv, pv, ntiles, BlendParams{}, 0, s);
 }
 
 static size_t unstage_lds(uint32_t tile) { return (size_t)tile * 12; }
@@ -1085,7 +1135,7 @@ __device__ __forceinline__ void bin_session(const BatchSession& S, uint32_t loca
 // (the batch instantiations that carry several bodies would spill heavily
 // under the same cap)
 template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer))))
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer, kX & kXWeight))))
 k_bin_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
   const BatchSession& S = ss[find_session(bg, k, blockIdx.x)];
   const uint32_t local = blockIdx.x - S.tile_begin;
@@ -1099,17 +1149,23 @@ k_bin_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
   bin_session<kThreads, kPer, 0, kX & kXFootprint>(S, local);
 }
 
-// 1024 threads per block when the widest session's partitions leave room
-// for one block per CU, else 512.
-template <int kThreads>
-__global__ void __launch_bounds__(kThreads) k_merge_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
+// As many threads per block as the widest session's partitions take; kVar: a
+// session keeps the luminance variance.
+template <int kThreads, bool kVar>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kVar ? 5 : 6))) k_merge_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
   const BatchSession& S = ss[find_session(bg, k, blockIdx.x)];
   const uint32_t local = blockIdx.x - S.part_begin;
   if (local >= S.nparts) return;
   const TableView tv = S.tv;
   const PartView pv = S.pv;
   const BlendParams bp = S.bp;
-  merge_body<true, kThreads>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
+  if constexpr (kVar) {
+    if (tv.var) {
+      merge_body<true, kThreads, true>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
+      return;
+    }
+  }
+  merge_body<true, kThreads, false>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
 }
 
 // A session whose queries are its records takes one unstage block per tile;
@@ -1161,13 +1217,31 @@ static hipError_t launch_bin_batch_x(uint32_t x, const BatchSession* d_ss, const
   }
 }
 
+template <int kThreads, bool kVar>
+static hipError_t launch_merge_batch_v(const BatchSession* d_ss, const uint32_t* bg, uint32_t k, uint32_t parts,
+                                       size_t lds, hipStream_t s) {
+  static LdsLimit lim;  // one per instantiation
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge_batch<kThreads, kVar>), lds, &lim);
+  if (e != hipSuccess) return e;
+  k_merge_batch<kThreads, kVar><<<parts, kThreads, lds, s>>>(d_ss, bg, k);
+  return hipGetLastError();
+}
+
+template <int kThreads>
+static hipError_t launch_merge_batch_t(bool var, const BatchSession* d_ss, const uint32_t* bg, uint32_t k,
+                                       uint32_t parts, size_t lds, hipStream_t s) {
+  return var ? launch_merge_batch_v<kThreads, true>(d_ss, bg, k, parts, lds, s)
+             : launch_merge_batch_v<kThreads, false>(d_ss, bg, k, parts, lds, s);
+}
+
 hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, const uint32_t* h_begins,
                         uint32_t stride, const BatchSession* h_ss, uint32_t k, hipStream_t s) {
   if (k == 0) return hipSuccess;
   if (k > stride) return hipErrorInvalidValue;
   uint32_t tiles = 0, parts = 0, qblks = 0, trans = 0;
   size_t lds_b = 0, lds_m = 0, lds_q = 0;
-  uint32_t x = 0;  // what any session's records carry
+  uint32_t x = 0, part_log2 = 0;  // what any session's records carry; the widest partitions
+  bool var = false;
   const uint32_t per = h_ss[0].pv.tile / 512;
   for (uint32_t i = 0; i < k; ++i) {
     const BatchSession& S = h_ss[i];
@@ -1183,6 +1257,8 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
     const size_t lb = bin_lds(P, S.pv.tile), lm = merge_lds(S.tv);
     lds_b = lb > lds_b ? lb : lds_b;
     lds_m = lm > lds_m ? lm : lds_m;
+    part_log2 = S.tv.part_log2 > part_log2 ? S.tv.part_log2 : part_log2;
+    var = var || S.tv.var;
     if ((S.fused_query != 0) != (S.pv.perm != nullptr)) return hipErrorInvalidValue;
     if (S.fused_query) {
       if (S.nq != S.n || S.nqblk != S.ntiles) return hipErrorInvalidValue;
@@ -1196,28 +1272,26 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
     qblks += S.nqblk;
     trans += S.ntrans;
   }
-  static LdsLimit lim_m[2], lim_q;
-  const bool wide = merge_wide(lds_m);
+  static LdsLimit lim_q;
   const uint32_t* bg_tile = d_begins;
   const uint32_t* bg_part = d_begins + stride;
   const uint32_t* bg_qblk = d_begins + 2 * stride;
   const uint32_t* bg_trans = d_begins + 3 * stride;
   hipError_t e = per == 8    ? launch_bin_batch_x<1024, 4>(x, d_ss, bg_tile, k, tiles, lds_b, s)
-                  : per == 12 ? launch_bin_batch_x<768, 8, 512, 12>(x, d_ss, bg_tile, k, tiles, lds_b, s)
+                  : per == 12 ? launch_bin_batch_x<512, 12>(x, d_ss, bg_tile, k, tiles, lds_b, s)
                               : launch_bin_batch_x<1024, 8>(x, d_ss, bg_tile, k, tiles, lds_b, s);
   if (e != hipSuccess) return e;
-  e = wide ? lds_limit(reinterpret_cast<const void*>(&k_merge_batch<1024>), lds_m, &lim_m[1])
-           : lds_limit(reinterpret_cast<const void*>(&k_merge_batch<kMergeThreads>), lds_m, &lim_m[0]);
-  if (e == hipSuccess) e = lds_limit(reinterpret_cast<const void*>(&k_query_batch), lds_q, &lim_q);
+  e = lds_limit(reinterpret_cast<const void*>(&k_query_batch), lds_q, &lim_q);
   if (e != hipSuccess) return e;
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (trans) k_transpose_batch<<<trans, kTransposeThreads, 0, s>>>(d_ss, bg_trans, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (wide)
-    k_merge_batch<1024><<<parts, 1024, lds_m, s>>>(d_ss, bg_part, k);
-  else
-    k_merge_batch<kMergeThreads><<<parts, kMergeThreads, lds_m, s>>>(d_ss, bg_part, k);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  switch (merge_threads(part_log2)) {
+    case 768: e = launch_merge_batch_t<768>(var, d_ss, bg_part, k, parts, lds_m, s); break;
+    case 384: e = launch_merge_batch_t<384>(var, d_ss, bg_part, k, parts, lds_m, s); break;
+    default: e = launch_merge_batch_t<192>(var, d_ss, bg_part, k, parts, lds_m, s); break;
+  }
+  if (e != hipSuccess) return e;
   if (qblks) k_query_batch<<<qblks, kQueryBlock, lds_q, s>>>(d_ss, bg_qblk, k);
   return hipGetLastError();
 }

@@ -17,7 +17,6 @@ __device__ __forceinline__ uint32_t xcd_partition(uint32_t b, uint32_t P) {
 }
 
 constexpr uint32_t kRunsPerLane = 4;  // consecutive tile runs each lane keeps in registers
-constexpr uint32_t kEntryBatch = 4;   // entries per lane loaded before processing
 
 // Largest lane l with excl[l] <= e, where excl is a non-decreasing per-lane
 // value (all lanes of the wave must call this).
@@ -39,22 +38,19 @@ __device__ __forceinline__ uint32_t wave_upper_bound(uint32_t excl, uint32_t e) 
 struct RunChunk {
   uint32_t pk[kRunsPerLane];
   uint32_t excl, total;
-  uint64_t cbase;
+  uint32_t cbase;
 };
 
 // Each wave of a merge block owns a contiguous slice [w_lo, w_hi) of the
-// tiles; it keeps up to 64 * kRunsPerLane of its partition's runs (offsets)
-// in registers.
+// tiles and takes its partition's runs there 64 * kRunsPerLane at a time.
 template <uint32_t kWaves>
 struct RunReader {
   const PartView& pv;
   uint32_t p, P, lane, w_lo, w_hi;
   const uint32_t *row_lo, *row_hi;
-  uint32_t r_lo[kRunsPerLane], r_hi[kRunsPerLane];
-  uint32_t loaded;  // chunk of runs held in registers
 
   __device__ __forceinline__ RunReader(const PartView& v, uint32_t part, uint32_t nparts, uint32_t ntiles)
-      : pv(v), p(part), P(nparts), lane(__lane_id()), loaded(~0u) {
+      : pv(v), p(part), P(nparts), lane(__lane_id()) {
     // (a multiple of 4 tiles, so that a lane's runs are one 16-byte load)
     const uint32_t per_wave = ((ntiles + kWaves - 1) / kWaves + 3u) & ~3u;
     w_lo = (threadIdx.x >> 6) * per_wave;
@@ -64,8 +60,9 @@ struct RunReader {
     row_hi = row_lo + stride;
   }
 
-  __device__ __forceinline__ void load_runs(uint32_t c0) {
+  __device__ __forceinline__ RunChunk chunk_of(uint32_t c0) const {
     const uint32_t t = c0 + lane * kRunsPerLane;  // a multiple of 4
+    uint32_t r_lo[kRunsPerLane], r_hi[kRunsPerLane];
     if (pv.runs_t) {
       // transposed table: two 16-byte loads (t + 3 < stride: inside the row)
       uint4 lo = make_uint4(0, 0, 0, 0), hi = make_uint4(0, 0, 0, 0);
@@ -94,11 +91,6 @@ struct RunReader {
         }
       }
     }
-    loaded = c0;
-  }
-
-  __device__ __forceinline__ RunChunk chunk_of(uint32_t c0) {
-    if (loaded != c0) load_runs(c0);
     RunChunk ch;
     uint32_t lt = 0;
 #pragma unroll
@@ -114,18 +106,19 @@ struct RunReader {
     }
     ch.excl = inc - lt;
     ch.total = (uint32_t)__shfl((int)inc, 63);
-    ch.cbase = (uint64_t)c0 * pv.tile;
+    ch.cbase = c0 * pv.tile;  // (staging holds fewer than 2^32 entries)
     return ch;
   }
 
   // The batch at entry e0 of a chunk: at[q] is the staging index of the
   // lane's q-th entry, ev[q] whether it exists (absent entries point at a
   // tile's first entry, so that every load stays branch-free and in
-  // bounds).  A batch takes the next 64 * kEntryBatch entries of the
-  // chunk's concatenated runs.
-  __device__ __forceinline__ void batch_of(const RunChunk& ch, uint32_t e0, uint64_t* at, bool* ev) const {
+  // bounds).  A batch takes the next 64 * kBatch entries of the chunk's
+  // concatenated runs.
+  template <uint32_t kBatch>
+  __device__ __forceinline__ void batch_of(const RunChunk& ch, uint32_t e0, uint32_t* at, bool* ev) const {
 #pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) {
+    for (uint32_t q = 0; q < kBatch; ++q) {
       const uint32_t e = e0 + q * 64 + lane;
       const uint32_t a = wave_upper_bound(ch.excl, e);
       const uint32_t r = e - (uint32_t)__shfl((int)ch.excl, (int)a);
@@ -141,25 +134,23 @@ struct RunReader {
       }
       ev[q] = e < ch.total;
       at[q] = ch.cbase +
-              (ev[q] ? (uint64_t)(a * kRunsPerLane + js) * pv.tile + (ps & 0xffffu) + (r - (ps >> 16)) : 0ull);
+              (ev[q] ? (a * kRunsPerLane + js) * pv.tile + (ps & 0xffffu) + (r - (ps >> 16)) : 0u);
     }
   }
 
-  // Calls body(at, ev, nb) for every batch of the wave's entries, in order
-  // (nb counts batches); returns the number of batches.
-  template <class F>
-  __device__ __forceinline__ uint32_t for_each_batch(F&& body) {
-    uint32_t nb = 0;
-    for (uint32_t c0 = w_lo; c0 < w_hi; c0 += 64 * kRunsPerLane) {
-      const RunChunk ch = chunk_of(c0);
-      for (uint32_t e0 = 0; e0 < ch.total; e0 += 64 * kEntryBatch, ++nb) {
-        bool ev[kEntryBatch];
-        uint64_t at[kEntryBatch];
-        batch_of(ch, e0, at, ev);
-        body(at, ev, nb);
+  // Calls body(at, ev) for every batch of kBatch entries a lane, in order;
+  // first is the slice's first chunk, e0 the entry of it to start at.
+  template <uint32_t kBatch, class F>
+  __device__ __forceinline__ void for_each_batch(const RunChunk& first, uint32_t e0, F&& body) const {
+    for (uint32_t c0 = w_lo; c0 < w_hi; c0 += 64 * kRunsPerLane, e0 = 0) {
+      const RunChunk ch = c0 == w_lo ? first : chunk_of(c0);
+      for (; e0 < ch.total; e0 += 64 * kBatch) {
+        bool ev[kBatch];
+        uint32_t at[kBatch];
+        batch_of<kBatch>(ch, e0, at, ev);
+        body(at, ev);
       }
     }
-    return nb;
   }
 };
 

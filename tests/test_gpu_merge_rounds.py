@@ -1,0 +1,56 @@
+"""Partitions with more touched cells than one round of the merge's sums
+holds: three quarters of every partition's slots touched in one frame, in
+plain, weighted and variance tables, fused (with the frame's own answers,
+rejected samples among them) and as separate calls, against the oracle."""
+import numpy as np
+import pytest
+
+from tests.helpers import to_device
+
+pytestmark = pytest.mark.gpu
+RTOL = 1e-5
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("kind,part_log2", [("plain", 12), ("plain", 11), ("plain", 8), ("weighted", 11),
+                                            ("variance", 10), ("variance", 11)])
+def test_dense_partitions_match_the_oracle(kind, part_log2, fused):
+    import oracle
+    from paper_2005_07547_amd import psf
+    from synth import workloads as W
+    wl = W.tiny(alpha_mode=W.ALPHA_PAPER)
+    sc = W.make_scene(wl)
+    cfg = dict(wl["table"], log2_slots=13, part_log2=part_log2, max_probe=1 << part_log2,
+               weighted=int(kind == "weighted"))
+    t = psf.Table(**cfg, flags=psf.PSF_FLAG_TRACK_VARIANCE if kind == "variance" else 0)
+    orc = oracle.Oracle(**cfg)
+    for it in range(3):
+        rec = dict(sc.generate(wl["gen"], it))
+        rec["rough"] = None
+        rec["r"][5::13] = np.nan  # rejected as samples, answered as queries
+        if kind == "weighted":
+            rec["weight"] = W.mis_weights(len(rec["px"]), seed=it)
+        d = to_device(rec)
+        if fused:
+            out, found = t.iterate(d)
+        else:
+            t.insert(d)
+            t.update()
+            out, found = t.query(d)
+        orc.insert(rec)
+        orc.update()
+        want, hit = orc.query(rec)
+        assert np.array_equal(found.cpu().numpy(), hit)
+        err = np.abs(out.cpu().numpy() - want) / np.maximum(np.abs(want), 1e-30)
+        assert float(err[:, hit.astype(bool)].max()) <= RTOL
+    st, ex, o = t.stats(), t.export(), orc.export()
+    # 8192 slots, an even spread of the cells: more in every partition than 5/16 of its slots
+    assert st["touched_last"] > 3000 and st["dropped"] == 0
+    assert np.array_equal(ex["keys"], o["keys"])
+    assert np.allclose(ex["c_old"].astype(np.float64), o["c_old"], rtol=1e-6 if kind == "weighted" else 0)
+    if kind == "variance":
+        keys, var = t.export_variance()
+        o_keys, o_var = orc.export_variance()
+        m = o["L"][0] * 0.25 + o["L"][1] * 0.5 + o["L"][2] * 0.25
+        assert np.array_equal(keys, o_keys)
+        assert np.all(np.abs(var - o_var) <= RTOL * (o_var + m * m) + 1e-30)
