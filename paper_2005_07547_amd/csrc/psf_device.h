@@ -273,43 +273,59 @@ __device__ __forceinline__ uint32_t octa_bin(float x, float y, float z, int32_t 
   return ((iu < top ? iu : top) << b) + (iw < top ? iw : top);
 }
 
-// Cell key of one vertex.  Returns false for rejected (non-finite) input.
-// has_rough is false when the caller supplied no roughness array (every
-// vertex diffuse); the direction is used only for glossy vertices.  With a
-// footprint (has_fp) the level comes from it (it must be finite and > 0),
-// else from the camera distance.  up > 0 asks for the cell that many levels
-// coarser (false if that passes max_level).
-//
-// The key decides nothing by branches on the lane's values: it is computed
-// for every lane, rejected ones too, and rejected at the end.  With early
-// exits (and four divisions) it took 212 vector instructions in 15 exec-mask
-// regions, and its scalar masks spilled in the binning pass.
-__device__ __forceinline__ bool cell_key(const KeyParams& kp, float px, float py, float pz, float nx,
-                                         float ny, float nz, float ox, float oy, float oz,
-                                         bool has_rough, float rough, bool has_fp, float fp,
-                                         uint64_t& key, bool& ovf, int32_t up = 0) {
-  int ok = (int)finite3(px, py, pz) & (int)finite3(nx, ny, nz);
-  int32_t lvl;
-  if (has_fp) {
-    ok &= (int)__builtin_isfinite(fp) & (int)(fp > 0.0f);
-    lvl = footprint_level(kp, fp);
-  } else {
-    lvl = cell_level(kp, px, py, pz);
-  }
-  lvl += up;
-  if (up > 0) ok &= (int)(lvl <= kp.max_level);
+// The parts of a cell key.  None decides anything by branches on the lane's
+// values: a key is computed for every lane, rejected ones too, and rejected
+// at the end.  (With early exits and four divisions it took 212 vector
+// instructions in 15 exec-mask regions, and its scalar masks spilled in the
+// binning pass.)
+
+// Level of a vertex, from its footprint (has_fp; it must be finite and > 0)
+// or the camera distance.
+__device__ __forceinline__ int32_t key_level(const KeyParams& kp, float px, float py, float pz, bool has_fp, float fp,
+                                             int& ok) {
+  if (!has_fp) return cell_level(kp, px, py, pz);
+  ok &= (int)__builtin_isfinite(fp) & (int)(fp > 0.0f);
+  return footprint_level(kp, fp);
+}
+
+// High word: the normal's bin, and at glossy vertices (has_rough and rough
+// below the threshold) the flag and the direction's bin.  has_rough is false
+// when the caller supplied no roughness array (every vertex diffuse); the
+// direction is used only for glossy vertices.
+__device__ __forceinline__ uint32_t key_normal(const KeyParams& kp, float nx, float ny, float nz) {
+  return octa_bin(nx, ny, nz, kp.nb_log2) << 16;
+}
+__device__ __forceinline__ uint32_t key_direction(const KeyParams& kp, float ox, float oy, float oz, bool has_rough,
+                                                  float rough, int& ok) {
+  if (!has_rough) return 0u;
+  const bool glossy = rough < kp.rough_thr;
+  ok &= (int)__builtin_isfinite(rough) & ((int)!glossy | (int)finite3(ox, oy, oz));
+  uint32_t hi = 0u;
+  if (__ballot(glossy)) hi = glossy ? (1u << 26) | (octa_bin(ox, oy, oz, kp.db_log2) << 20) : 0u;
+  return hi;
+}
+
+// The whole key from the high word's bins and the position at a level.
+__device__ __forceinline__ uint64_t key_at(const KeyParams& kp, float px, float py, float pz, int32_t lvl, uint32_t hi,
+                                           bool& ovf) {
   const int32_t shift = kp.e_min + lvl;
   float fx, fy, fz;
   const uint32_t ix = grid16(px, shift, fx), iy = grid16(py, shift, fy), iz = grid16(pz, shift, fz);
   // a coordinate outside [-2^15, 2^15): an integer f with |f + 1/2| > 2^15 - 1/2
   ovf = fmaxf(fmaxf(fabsf(fx + 0.5f), fabsf(fy + 0.5f)), fabsf(fz + 0.5f)) > 32767.5f;
-  uint32_t hi = ((uint32_t)lvl << 27) | (octa_bin(nx, ny, nz, kp.nb_log2) << 16) | iz;
-  if (has_rough) {
-    const bool glossy = rough < kp.rough_thr;
-    ok &= (int)__builtin_isfinite(rough) & ((int)!glossy | (int)finite3(ox, oy, oz));
-    if (__ballot(glossy)) hi |= glossy ? (1u << 26) | (octa_bin(ox, oy, oz, kp.db_log2) << 20) : 0u;
-  }
-  key = ((uint64_t)hi << 32) | (iy << 16) | ix;
+  hi |= ((uint32_t)lvl << 27) | iz;
+  return ((uint64_t)hi << 32) | (iy << 16) | ix;
+}
+
+// Cell key of one vertex.  Returns false for rejected (non-finite) input.
+__device__ __forceinline__ bool cell_key(const KeyParams& kp, float px, float py, float pz, float nx,
+                                         float ny, float nz, float ox, float oy, float oz,
+                                         bool has_rough, float rough, bool has_fp, float fp,
+                                         uint64_t& key, bool& ovf) {
+  int ok = (int)finite3(px, py, pz) & (int)finite3(nx, ny, nz);
+  const int32_t lvl = key_level(kp, px, py, pz, has_fp, fp, ok);
+  const uint32_t hi = key_normal(kp, nx, ny, nz) | key_direction(kp, ox, oy, oz, has_rough, rough, ok);
+  key = key_at(kp, px, py, pz, lvl, hi, ovf);
   return ok != 0;
 }
 
@@ -468,21 +484,61 @@ __device__ __forceinline__ float ld_once_at(const float* p, uint32_t i) {
 }
 __device__ __forceinline__ void st_once(float* p, float v) { __builtin_nontemporal_store(v, p); }
 
-// Key of query i of a structure-of-arrays query set (kEmpty if rejected).
+// One vertex of a structure-of-arrays query set: element i of the arrays
+// from a wave-uniform start on.  Every load is unconditional (absent arrays
+// alias the positions) and all are waited for together: under the key's
+// conditions they would be one dependent round trip after another.
+struct Vertex {
+  float p[3], n[3], o[3], rough, fp;
+};
 template <class Q>
-__device__ __forceinline__ uint64_t query_key(const KeyParams& kp, const Q& q, uint64_t i, int32_t up = 0) {
-  const bool hr = q.rough != nullptr;
-  const float ro = hr ? ld_once(q.rough + i) : 0.0f;
-  const bool gl = hr && ro < kp.rough_thr;
-  const bool hf = q.footprint != nullptr;
+__device__ __forceinline__ Vertex load_vertex(const Q& q, uint64_t start, uint32_t i) {
+  const bool hr = q.rough != nullptr, hf = q.footprint != nullptr;
+  Vertex v;
+  v.p[0] = ld_once_at(q.px + start, i);
+  v.p[1] = ld_once_at(q.py + start, i);
+  v.p[2] = ld_once_at(q.pz + start, i);
+  v.n[0] = ld_once_at(q.nx + start, i);
+  v.n[1] = ld_once_at(q.ny + start, i);
+  v.n[2] = ld_once_at(q.nz + start, i);
+  v.o[0] = v.o[1] = v.o[2] = v.rough = v.fp = 0.0f;
+  if (hr) {
+    v.o[0] = ld_once_at(q.ox + start, i);
+    v.o[1] = ld_once_at(q.oy + start, i);
+    v.o[2] = ld_once_at(q.oz + start, i);
+    v.rough = ld_once_at(q.rough + start, i);
+  }
+  if (hf) v.fp = ld_once_at(q.footprint + start, i);
+  return v;
+}
+
+// (an empty statement that uses the values, so their loads issue before it)
+__device__ __forceinline__ void loaded(const Vertex& v) {
+  asm volatile("" : : "v"(v.p[0]), "v"(v.p[1]), "v"(v.p[2]), "v"(v.n[0]), "v"(v.n[1]), "v"(v.n[2]));
+  asm volatile("" : : "v"(v.o[0]), "v"(v.o[1]), "v"(v.o[2]), "v"(v.rough), "v"(v.fp));
+}
+
+// Key of a loaded vertex (kEmpty if rejected).
+template <class Q>
+__device__ __forceinline__ uint64_t vertex_key(const KeyParams& kp, const Q& q, const Vertex& v) {
   uint64_t key;
   bool ovf;
-  if (!cell_key(kp, ld_once(q.px + i), ld_once(q.py + i), ld_once(q.pz + i), ld_once(q.nx + i),
-                ld_once(q.ny + i), ld_once(q.nz + i), gl ? ld_once(q.ox + i) : 0.0f,
-                gl ? ld_once(q.oy + i) : 0.0f, gl ? ld_once(q.oz + i) : 0.0f, hr, ro, hf,
-                hf ? ld_once(q.footprint + i) : 0.0f, key, ovf, up))
-    return kEmpty;
-  return key;
+  const bool ok = cell_key(kp, v.p[0], v.p[1], v.p[2], v.n[0], v.n[1], v.n[2], v.o[0], v.o[1], v.o[2],
+                           q.rough != nullptr, v.rough, q.footprint != nullptr, v.fp, key, ovf);
+  return ok ? key : kEmpty;
+}
+
+// Block order of the lookup passes.  Blocks are dispatched to the 8 XCDs
+// round-robin; each XCD takes 64 consecutive blocks of every 512, so that
+// the cells neighbouring scanlines share are fetched into one L2 (the last,
+// incomplete group keeps the launch order).  With the loads in one round
+// trip: lookup of 2,073,600 first vertices with fallback levels 46.0 -> 36.8
+// us, estimates at 3,686,400 vertices 188 -> 159 us, 2,073,600 lookups at
+// scattered vertices 51.6 -> 49.8 us (those wait on the misses of their
+// slots).
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t blocks) {
+  const uint32_t g = b & ~511u, r = b & 511u;
+  return g + 512 <= blocks ? g + (r & 7u) * 64 + (r >> 3) : b;
 }
 
 // Eq. 10-11 for one cell, FP32, on counter words (counts, or weight sums

@@ -243,10 +243,14 @@ __global__ void __launch_bounds__(256) k_update(TableView tv, BlendParams bp, ui
 // ------------------------------------------------------------------ query
 __global__ void __launch_bounds__(256) k_query(QryPtrs q, uint64_t n, KeyParams kp, TableView tv,
                                                int32_t dtype, float* out, uint8_t* found) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
+  const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
+  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  loaded(v);
   float rgb[3];
-  const uint8_t hit = lookup_key(tv, dtype, query_key(kp, q, i), rgb);
+  const uint8_t hit = lookup_key(tv, dtype, vertex_key(kp, q, v), rgb);
+  if (threadIdx.x > last) return;
+  const uint64_t i = start + threadIdx.x;
   st_once(out + i, rgb[0]);
   st_once(out + n + i, rgb[1]);
   st_once(out + 2 * n + i, rgb[2]);
@@ -260,21 +264,29 @@ __global__ void __launch_bounds__(256) k_query(QryPtrs q, uint64_t n, KeyParams 
 __global__ void __launch_bounds__(256) k_query_hier(QryPtrs q, uint64_t n, uint32_t up, KeyParams kp,
                                                     TableView tv, int32_t dtype, float* out,
                                                     uint8_t* level_out) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
+  const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
+  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  loaded(v);
+  // the bins once, the position at each level
+  int ok = (int)finite3(v.p[0], v.p[1], v.p[2]) & (int)finite3(v.n[0], v.n[1], v.n[2]);
+  const int32_t lvl = key_level(kp, v.p[0], v.p[1], v.p[2], q.footprint != nullptr, v.fp, ok);
+  const uint32_t hi = key_normal(kp, v.n[0], v.n[1], v.n[2]) |
+                      key_direction(kp, v.o[0], v.o[1], v.o[2], q.rough != nullptr, v.rough, ok);
   float rgb[3] = {0.0f, 0.0f, 0.0f};
   uint8_t lv = 0;
-  for (uint32_t k = 0; k <= up; ++k) {
-    const uint64_t key = query_key(kp, q, i, (int32_t)k);
-    if (key == kEmpty) break;  // invalid vertex, or past the coarsest level
-    if (lookup_key(tv, dtype, key, rgb)) {
+  for (uint32_t k = 0; ok && k <= up && lvl + (int32_t)k <= kp.max_level; ++k) {
+    bool ovf;
+    if (lookup_key(tv, dtype, key_at(kp, v.p[0], v.p[1], v.p[2], lvl + (int32_t)k, hi, ovf), rgb)) {
       lv = (uint8_t)(k + 1);
       break;
     }
   }
-  out[i] = rgb[0];
-  out[n + i] = rgb[1];
-  out[2 * n + i] = rgb[2];
+  if (threadIdx.x > last) return;
+  const uint64_t i = start + threadIdx.x;
+  st_once(out + i, rgb[0]);
+  st_once(out + n + i, rgb[1]);
+  st_once(out + 2 * n + i, rgb[2]);
   if (level_out) level_out[i] = lv;
 }
 
@@ -282,52 +294,72 @@ __global__ void __launch_bounds__(256) k_query_hier(QryPtrs q, uint64_t n, uint3
 // Sec. 4.2 (Eq. 25) and Sec. 5 (Eq. 28): the control variate h = f~L_i(x,
 // w_i) has the known integral L~o\e(x, w_o).  mode 0: wp (g - beta h) +
 // beta L; mode 1: gamma wp (g - h) + L.  Either cell missing: wp g.
-constexpr uint32_t kEstThreads = 256, kEstPerThread = 1;
+constexpr uint32_t kEstThreads = 256;
 
 __global__ void __launch_bounds__(kEstThreads) k_estimate(EstPtrs a, uint64_t n, KeyParams kp_o,
                                                           TableView tv_o, int32_t dt_o, KeyParams kp_i,
                                                           TableView tv_i, int32_t dt_i, int32_t mode,
                                                           float param, float* out, uint8_t* applied) {
-  // kEstPerThread vertices per thread: all their first probes (two per
-  // vertex) are in flight together; indices past the end read the last
-  // vertex and write nothing
-  const uint64_t i0 = (uint64_t)blockIdx.x * (kEstThreads * kEstPerThread) + threadIdx.x;
-  PendingLookup lo[kEstPerThread], li[kEstPerThread];
-#pragma unroll
-  for (uint32_t v = 0; v < kEstPerThread; ++v) {
-    const uint64_t i = i0 + (uint64_t)v * kEstThreads;
-    const uint64_t ic = i < n ? i : n - 1;
-    lo[v] = lookup_first(tv_o, query_key(kp_o, a.qo, ic));
-    li[v] = lookup_first(tv_i, query_key(kp_i, a.qi, ic));
+  // a vertex's two first probes are in flight together; indices past the
+  // end read the last vertex and write nothing
+  const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * kEstThreads;
+  const uint32_t last = n - start < kEstThreads ? (uint32_t)(n - start) - 1 : kEstThreads - 1;
+  const uint32_t t = threadIdx.x < last ? threadIdx.x : last;
+  const bool hr = a.qo.rough != nullptr, hf = a.qo.footprint != nullptr;
+  const Vertex v = load_vertex(a.qo, start, t);
+  float wi[3] = {0.0f, 0.0f, 0.0f};
+  if (hr) {
+    wi[0] = ld_once_at(a.qi.ox + start, t);
+    wi[1] = ld_once_at(a.qi.oy + start, t);
+    wi[2] = ld_once_at(a.qi.oz + start, t);
   }
+  const float g[3] = {ld_once_at(a.gr + start, t), ld_once_at(a.gg + start, t), ld_once_at(a.gb + start, t)};
+  const float w = ld_once_at(a.wp + start, t);
+  loaded(v);
+  asm volatile("" : : "v"(wi[0]), "v"(wi[1]), "v"(wi[2]));
+  // the two keys share the position and normal where the tables share their
+  // grid (the fields of one frame do)
+  const bool same = kp_o.cx == kp_i.cx && kp_o.cy == kp_i.cy && kp_o.cz == kp_i.cz && kp_o.kappa == kp_i.kappa &&
+                    kp_o.e_min == kp_i.e_min && kp_o.max_level == kp_i.max_level && kp_o.nb_log2 == kp_i.nb_log2;
+  int ok_o = (int)finite3(v.p[0], v.p[1], v.p[2]) & (int)finite3(v.n[0], v.n[1], v.n[2]);
+  int ok_i = ok_o;
+  bool ovf;
+  const int32_t lvl_o = key_level(kp_o, v.p[0], v.p[1], v.p[2], hf, v.fp, ok_o);
+  uint64_t key_o = key_at(kp_o, v.p[0], v.p[1], v.p[2], lvl_o, key_normal(kp_o, v.n[0], v.n[1], v.n[2]), ovf);
+  uint64_t key_i = key_o;
+  if (same) {
+    ok_i = ok_o;
+  } else {
+    const int32_t lvl_i = key_level(kp_i, v.p[0], v.p[1], v.p[2], hf, v.fp, ok_i);
+    key_i = key_at(kp_i, v.p[0], v.p[1], v.p[2], lvl_i, key_normal(kp_i, v.n[0], v.n[1], v.n[2]), ovf);
+  }
+  key_o |= (uint64_t)key_direction(kp_o, v.o[0], v.o[1], v.o[2], hr, v.rough, ok_o) << 32;
+  const PendingLookup lo = lookup_first(tv_o, ok_o ? key_o : kEmpty);
+  key_i |= (uint64_t)key_direction(kp_i, wi[0], wi[1], wi[2], hr, v.rough, ok_i) << 32;
+  const PendingLookup li = lookup_first(tv_i, ok_i ? key_i : kEmpty);
+  float L[3], h[3];
+  const uint8_t fo = lookup_finish(tv_o, dt_o, lo, L);
+  const uint8_t fi = lookup_finish(tv_i, dt_i, li, h);
+  if (threadIdx.x > last) return;
+  const bool both = fo && fi;
+  float e[3];
 #pragma unroll
-  for (uint32_t v = 0; v < kEstPerThread; ++v) {
-    const uint64_t i = i0 + (uint64_t)v * kEstThreads;
-    if (i >= n) break;
-    float L[3], h[3];
-    const uint8_t fo = lookup_finish(tv_o, dt_o, lo[v], L);
-    const uint8_t fi = lookup_finish(tv_i, dt_i, li[v], h);
-    const float g[3] = {ld_once(a.gr + i), ld_once(a.gg + i), ld_once(a.gb + i)};
-    const float w = ld_once(a.wp + i);
-    const bool both = fo && fi;
-    float e[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (!both) {
-        e[c] = w * g[c];
-      } else if (mode == 0) {
-        const float corr = w * (g[c] - param * h[c]);
-        e[c] = corr + param * L[c];
-      } else {
-        const float corr = param * (w * (g[c] - h[c]));
-        e[c] = corr + L[c];
-      }
+  for (int c = 0; c < 3; ++c) {
+    if (!both) {
+      e[c] = w * g[c];
+    } else if (mode == 0) {
+      const float corr = w * (g[c] - param * h[c]);
+      e[c] = corr + param * L[c];
+    } else {
+      const float corr = param * (w * (g[c] - h[c]));
+      e[c] = corr + L[c];
     }
-    st_once(out + i, e[0]);
-    st_once(out + n + i, e[1]);
-    st_once(out + 2 * n + i, e[2]);
-    if (applied) applied[i] = both ? 1 : 0;
   }
+  const uint64_t i = start + threadIdx.x;
+  st_once(out + i, e[0]);
+  st_once(out + n + i, e[1]);
+  st_once(out + 2 * n + i, e[2]);
+  if (applied) applied[i] = both ? 1 : 0;
 }
 
 // ------------------------------------------------------------------ progressive solver
@@ -335,14 +367,23 @@ __global__ void __launch_bounds__(kEstThreads) k_estimate(EstPtrs a, uint64_t n,
 // at the next vertex once: Lbar = L_e + L~(x_{i+1}) * f G w / p.
 __global__ void __launch_bounds__(256) k_step_samples(StepPtrs a, uint64_t n, KeyParams kp, TableView tv,
                                                       int32_t dtype, float* out) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float L[3];
-  lookup_key(tv, dtype, query_key(kp, a.next, i), L);
+  const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
+  const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
+  const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
+  const Vertex v = load_vertex(a.next, start, ti);
   const bool le = a.le_r != nullptr;
-  const float e[3] = {le ? ld_once(a.le_r + i) : 0.0f, le ? ld_once(a.le_g + i) : 0.0f,
-                      le ? ld_once(a.le_b + i) : 0.0f};
-  const float t[3] = {ld_once(a.t_r + i), ld_once(a.t_g + i), ld_once(a.t_b + i)};
+  float e[3] = {0.0f, 0.0f, 0.0f};
+  if (le) {
+    e[0] = ld_once_at(a.le_r + start, ti);
+    e[1] = ld_once_at(a.le_g + start, ti);
+    e[2] = ld_once_at(a.le_b + start, ti);
+  }
+  const float t[3] = {ld_once_at(a.t_r + start, ti), ld_once_at(a.t_g + start, ti), ld_once_at(a.t_b + start, ti)};
+  loaded(v);
+  float L[3];
+  lookup_key(tv, dtype, vertex_key(kp, a.next, v), L);
+  if (threadIdx.x > last) return;
+  const uint64_t i = start + threadIdx.x;
 #pragma unroll
   for (int c = 0; c < 3; ++c) out[(uint64_t)c * n + i] = e[c] + L[c] * t[c];
 }
@@ -755,9 +796,11 @@ __global__ void __launch_bounds__(256) k_update_sh(TableView tv, BlendParams bp,
 // Lookup: the luminance at the query's normal and the chroma, as RGB.
 __global__ void __launch_bounds__(256) k_query_sh(QryPtrs q, uint64_t n, KeyParams kp, TableView tv, float* out,
                                                   uint8_t* found) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t key = query_key(kp, q, i);
+  const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
+  const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
+  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  loaded(v);
+  const uint64_t key = vertex_key(kp, q, v);
   float rgb[3] = {0.0f, 0.0f, 0.0f};
   uint8_t hit = 0;
   if (key != kEmpty) {
@@ -765,17 +808,19 @@ __global__ void __launch_bounds__(256) k_query_sh(QryPtrs q, uint64_t n, KeyPara
     if (s != ~0ull && tv.slots[s].c_old != 0) {
       const ShState st = tv.sh[s];
       const float k0 = 0.28209479177387814f, k1 = 0.4886025119029199f;
-      const float y = ((st.c[0] * k0 + st.c[1] * (k1 * q.ny[i])) + st.c[2] * (k1 * q.nz[i])) +
-                      st.c[3] * (k1 * q.nx[i]);
+      const float y = ((st.c[0] * k0 + st.c[1] * (k1 * v.n[1])) + st.c[2] * (k1 * v.n[2])) +
+                      st.c[3] * (k1 * v.n[0]);
       rgb[0] = (y + st.co) - st.cg;
       rgb[1] = y + st.cg;
       rgb[2] = (y - st.co) - st.cg;
       hit = 1;
     }
   }
-  out[i] = rgb[0];
-  out[n + i] = rgb[1];
-  out[2 * n + i] = rgb[2];
+  if (threadIdx.x > last) return;
+  const uint64_t i = start + threadIdx.x;
+  st_once(out + i, rgb[0]);
+  st_once(out + n + i, rgb[1]);
+  st_once(out + 2 * n + i, rgb[2]);
   if (found) found[i] = hit;
 }
 
@@ -849,6 +894,7 @@ hipError_t launch_update(const TableView& tv, const BlendParams& bp, uint64_t ns
 
 hipError_t launch_query(const QryPtrs& q, uint64_t n, const KeyParams& kp, const TableView& tv,
                         int32_t dtype, float* out, uint8_t* found, hipStream_t s) {
+  if (n == 0) return hipSuccess;
   k_query<<<grid_for(n, 256), 256, 0, s>>>(q, n, kp, tv, dtype, out, found);
   return hipGetLastError();
 }
@@ -857,7 +903,7 @@ hipError_t launch_estimate(const EstPtrs& a, uint64_t n, const KeyParams& kp_o, 
                            int32_t dt_o, const KeyParams& kp_i, const TableView& tv_i, int32_t dt_i,
                            int32_t mode, float param, float* out, uint8_t* applied, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_estimate<<<grid_for(n, kEstThreads * kEstPerThread), kEstThreads, 0, s>>>(a, n, kp_o, tv_o, dt_o, kp_i, tv_i,
+  k_estimate<<<grid_for(n, kEstThreads), kEstThreads, 0, s>>>(a, n, kp_o, tv_o, dt_o, kp_i, tv_i,
                                                                              dt_i, mode, param, out, applied);
   return hipGetLastError();
 }

@@ -867,6 +867,14 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
 // keeps the variance holds one more value an entry: 20 at 96).
 static uint32_t merge_threads(uint32_t part_log2) { return part_log2 >= 12 ? 768u : part_log2 == 11 ? 384u : 192u; }
 
+// The same for a launch of P partitions that does not fill 256 CUs: twice or
+// four times the threads, as far as they fit.
+static uint32_t merge_threads(uint32_t part_log2, uint32_t P) {
+  uint32_t t = merge_threads(part_log2);
+  while (t < 768 && (uint64_t)P * t * 2 <= 256ull * 24 * 64) t *= 2;
+  return t;
+}
+
 template <bool kFused, int kThreads, bool kVar>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kVar ? 5 : 6)))
 k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp, int32_t results) {
@@ -1031,7 +1039,7 @@ static hipError_t launch_merge_t(const TableView& tv, const PartView& pv, uint32
 template <bool kFused, bool kVar>
 static hipError_t launch_merge_f(const TableView& tv, const PartView& pv, uint32_t ntiles, const BlendParams& bp,
                                  int32_t results, hipStream_t s) {
-  switch (merge_threads(tv.part_log2)) {
+  switch (merge_threads(tv.part_log2, 1u << (tv.log2_slots - tv.part_log2))) {
     case 768: return launch_merge_t<kFused, 768, kVar>(tv, pv, ntiles, bp, results, s);
     case 384: return launch_merge_t<kFused, 384, kVar>(tv, pv, ntiles, bp, results, s);
     default: return launch_merge_t<kFused, 192, kVar>(tv, pv, ntiles, bp, results, s);
@@ -1183,13 +1191,18 @@ __global__ void __launch_bounds__(kQueryBlock) k_query_batch(const BatchSession*
     return;
   }
   const uint64_t nq = S.nq;
-  const uint64_t i = (uint64_t)local * kQueryBlock + threadIdx.x;
-  if (i >= nq) return;
+  const uint64_t start = (uint64_t)local * kQueryBlock;
+  if (start >= nq) return;
+  const uint32_t last = nq - start < kQueryBlock ? (uint32_t)(nq - start) - 1 : kQueryBlock - 1;
   const TableView tv = S.tv;
   const KeyParams kp = S.kp;
   const QryPtrs q = S.q;
+  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  loaded(v);
   float rgb[3];
-  const uint8_t hit = lookup_key(tv, S.bp.dtype, query_key(kp, q, i), rgb);
+  const uint8_t hit = lookup_key(tv, S.bp.dtype, vertex_key(kp, q, v), rgb);
+  if (threadIdx.x > last) return;
+  const uint64_t i = start + threadIdx.x;
   out[i] = rgb[0];
   out[nq + i] = rgb[1];
   out[2 * nq + i] = rgb[2];
