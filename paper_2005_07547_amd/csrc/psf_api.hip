@@ -1,6 +1,7 @@
 // C-ABI layer of the PSTF hash library: argument validation, memory layout,
 // strategy selection and kernel launches.  Nothing here throws across the
 // ABI; every entry point returns a psf_status.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -232,6 +233,9 @@ Layout layout_of(const psf_config& c) {
     L.cap = c.max_batch ? c.max_batch : kDefaultBatch;
     L.tiles = (uint32_t)((L.cap + tile - 1) / tile);
     L.cap = (uint64_t)L.tiles * tile;
+    // rows of the offset tables: also the smaller tiles of a small launch
+    const uint64_t small = (L.cap + 1023) / 1024;
+    if (!c.bin_per) L.tiles = (uint32_t)std::max<uint64_t>(L.tiles, std::min<uint64_t>(small, psf::kSmallTiles));
     L.stage_key = off;
     off = align_up(off + L.cap * 8, 256);
     L.stage_v = off;
@@ -301,6 +305,12 @@ psf::RecPtrs offset_rec(const psf::RecPtrs& rp, uint64_t off) {
   return sub;
 }
 
+// Records per tile of a launch of n records: the caller's binning width, or
+// by the launch's size.
+uint32_t tile_for(const psf_table* t, uint64_t n) {
+  return t->cfg.bin_per ? t->pv.tile : psf::launch_tile(n, 1u << (t->cfg.log2_slots - t->tv.part_log2));
+}
+
 // Whether a partitioned launch of ntiles tiles transposes its run table.
 bool transpose_runs(const psf_table* t, uint32_t ntiles) {
   return (t->cfg.flags & PSF_FLAG_TRANSPOSE_RUNS) ||
@@ -316,6 +326,7 @@ psf_status do_insert(psf_table* t, const psf::RecPtrs& rp, uint64_t n, hipStream
       psf::PartView pv = t->pv;
       pv.perm = nullptr;
       pv.weights = sub.weight != nullptr;
+      pv.tile = tile_for(t, m);
       const uint32_t nt = (uint32_t)((m + pv.tile - 1) / pv.tile);
       if (!transpose_runs(t, nt)) pv.runs_t = nullptr;
       e = timed(t, PSF_K_BIN, s, [&] { return psf::launch_bin(sub, m, t->kp, t->tv, pv, s); });
@@ -541,6 +552,7 @@ PSF_API psf_status psf_iterate(psf_table* t, const psf_records* rec, uint64_t n,
     psf::PartView pv = t->pv;
     if (!fq) pv.perm = nullptr;
     pv.weights = rp.weight != nullptr;
+    pv.tile = tile_for(t, n);
     const uint32_t nt = (uint32_t)((n + pv.tile - 1) / pv.tile);
     if (!transpose_runs(t, nt)) pv.runs_t = nullptr;
     hipError_t e = timed(t, PSF_K_BIN, s, [&] { return psf::launch_bin(rp, n, t->kp, t->tv, pv, s); });

@@ -141,6 +141,8 @@ constexpr uint32_t kDroppedBits = 0xffffffffu;
 constexpr unsigned long long kLookupOnlyBit = 1ull << 63;
 bool bin_per_ok(uint32_t per);          // supported records per thread of the binning pass
 uint32_t bin_tile(uint32_t per);        // records per binning tile
+constexpr uint32_t kSmallTiles = 512;    // most tiles of a launch that takes smaller ones
+uint32_t launch_tile(uint64_t n, uint32_t nparts);  // records per tile at the default width
 uint32_t update_grid(uint64_t nslots);  // blocks of the streaming update
 
 // One session of a batched iteration (device copy read by the batch kernels).

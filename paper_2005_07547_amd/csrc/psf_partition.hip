@@ -48,6 +48,19 @@ bool bin_per_ok(uint32_t per) { return per == 8 || per == 12 || per == 16; }
 __host__ __device__ constexpr size_t bin_lds_per_record(uint32_t tile) { return tile <= 4096 ? 16 : 12; }
 uint32_t bin_tile(uint32_t per) { return 512 * per; }
 
+// Records per tile of a launch of n records at the default binning width.
+// Tiles of 4096 records fill the 256 CUs from a million records on; a smaller
+// launch takes tiles of 2048 or 1024 (up to kSmallTiles of them, two a CU),
+// while a tile is still twice the partitions whose counters each tile scans
+// and writes.  8,192 records: bin 14.9 -> 7.2, merge 12.9 -> 10.7, answers 5.1
+// -> 4.0 us; 250,749: 21.4 -> 10.7, 16.7 -> 17.0, 8.1 -> 4.8; 921,600 of the SH
+// payload (tiles of 2048): bin 32.4 -> 25.1.
+uint32_t launch_tile(uint64_t n, uint32_t nparts) {
+  for (uint32_t tile = 1024; tile < 4096; tile *= 2)
+    if (n <= (uint64_t)kSmallTiles * tile && 2 * nparts <= tile) return tile;
+  return 4096;
+}
+
 // Exclusive prefix sum of cnt[0..m) in LDS, in place; returns the total.
 // Called by all kThreads threads of the block.
 template <int kThreads>
@@ -135,8 +148,8 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
 }
 
 // Threads and records per thread of the binning pass: a tile of 4096 records
-// takes 1024 threads with 4 records each (6144: 768 with 8, weighted 512
-// with 12; 8192: 1024 with 8).  The pass waits on one dependent step after
+// takes 1024 threads with 4 records each (6144: 768 with 8, or 512 with 12
+// where records carry more; 8192: 1024 with 8).  The pass waits on one dependent step after
 // another (record loads, LDS ranks, scan, staging), so twice the wavefronts
 // with half the records each hide more of it: 70.6 -> 62.0 us for 3,686,400
 // records (900 tiles) against 512 threads with 8, 174 -> 163 us for 1688
@@ -888,7 +901,7 @@ k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp, int32_t resu
 // four consecutive records at a time (8-byte perm loads, 16-byte stores when
 // the output rows are 16-byte aligned; non-temporal, since no kernel of the
 // iteration reads the answers again).
-constexpr uint32_t kUnstageThreads = 512;
+constexpr uint32_t kUnstageThreads = 512;  // (256 for the 1024-record tiles of small launches)
 
 __device__ __forceinline__ void unstage_one(const float* s_res, uint32_t count, uint32_t pos, float& r,
                                             float& g, float& b, uint8_t& f) {
@@ -969,9 +982,13 @@ static size_t merge_lds(const TableView& tv) {
   return merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv));
 }
 
+static bool tile_ok(uint32_t tile) {
+  return tile == 1024 || tile == 2048 || (tile % 512 == 0 && bin_per_ok(tile / 512));
+}
+
 bool partition_ok(const TableView& tv, const PartView& pv, uint64_t n) {
-  return n <= pv.capacity && tv.part_log2 <= kMaxPartLog2 && pv.tile % 512 == 0 &&
-         bin_per_ok(pv.tile / 512) && (1u << (tv.log2_slots - tv.part_log2)) <= kTouchEntries;
+  return n <= pv.capacity && tv.part_log2 <= kMaxPartLog2 && tile_ok(pv.tile) &&
+         (n + pv.tile - 1) / pv.tile <= pv.max_tiles && (1u << (tv.log2_slots - tv.part_log2)) <= kTouchEntries;
 }
 
 template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
@@ -984,15 +1001,15 @@ static hipError_t launch_bin_t(const RecPtrs& rec, uint64_t n, const KeyParams& 
   return hipGetLastError();
 }
 
-template <uint32_t kThreads, uint32_t kPer, uint32_t kThreadsW = kThreads, uint32_t kPerW = kPer>
+template <uint32_t kAlso, uint32_t kThreads, uint32_t kPer, uint32_t kThreadsX = kThreads, uint32_t kPerX = kPer>
 static hipError_t launch_bin_x(uint32_t x, const RecPtrs& rec, uint64_t n, const KeyParams& kp,
                                const TableView& tv, const PartView& pv, size_t shm, uint32_t ntiles,
                                hipStream_t s) {
   switch (x) {
-    case 0: return launch_bin_t<kThreads, kPer, 0>(rec, n, kp, tv, pv, shm, ntiles, s);
-    case kXFootprint: return launch_bin_t<kThreads, kPer, kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
-    case kXWeight: return launch_bin_t<kThreadsW, kPerW, kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
-    default: return launch_bin_t<kThreadsW, kPerW, kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case 0: return launch_bin_t<kThreads, kPer, kAlso>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case kXFootprint: return launch_bin_t<kThreadsX, kPerX, kAlso | kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
+    case kXWeight: return launch_bin_t<kThreadsX, kPerX, kAlso | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    default: return launch_bin_t<kThreadsX, kPerX, kAlso | kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
   }
 }
 
@@ -1006,23 +1023,26 @@ hipError_t launch_bin(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const
   if (n == 0) return hipSuccess;
   if (!partition_ok(tv, pv, n)) return hipErrorInvalidValue;
   const uint32_t P = 1u << (tv.log2_slots - tv.part_log2);
-  const uint32_t per = pv.tile / 512;
   const uint32_t ntiles = (uint32_t)((n + pv.tile - 1) / pv.tile);
   const size_t shm = bin_lds(P, pv.tile);
   const uint32_t x = record_extras(rec);
   if ((x & kXWeight) && !weighted(tv)) return hipErrorInvalidValue;
   if (tv.sh) {
-    if (per != 8 || !pv.stage_n || pv.perm) return hipErrorInvalidValue;
-    switch (x) {
-      case 0: return launch_bin_t<1024, 4, kXNormal>(rec, n, kp, tv, pv, shm, ntiles, s);
-      case kXFootprint: return launch_bin_t<1024, 4, kXNormal | kXFootprint>(rec, n, kp, tv, pv, shm, ntiles, s);
-      case kXWeight: return launch_bin_t<1024, 4, kXNormal | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
-      default: return launch_bin_t<1024, 4, kXNormal | kXFootprint | kXWeight>(rec, n, kp, tv, pv, shm, ntiles, s);
+    if (!pv.stage_n || pv.perm) return hipErrorInvalidValue;
+    switch (pv.tile) {
+      case 1024: return launch_bin_x<kXNormal, 1024, 1>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+      case 2048: return launch_bin_x<kXNormal, 1024, 2>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+      case 4096: return launch_bin_x<kXNormal, 1024, 4>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+      default: return hipErrorInvalidValue;
     }
   }
-  if (per == 8) return launch_bin_x<1024, 4>(x, rec, n, kp, tv, pv, shm, ntiles, s);
-  if (per == 12) return launch_bin_x<768, 8, 512, 12>(x, rec, n, kp, tv, pv, shm, ntiles, s);
-  return launch_bin_x<1024, 8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+  switch (pv.tile) {
+    case 1024: return launch_bin_x<0, 1024, 1>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+    case 2048: return launch_bin_x<0, 1024, 2>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+    case 4096: return launch_bin_x<0, 1024, 4>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+    case 6144: return launch_bin_x<0, 768, 8, 512, 12>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+    default: return launch_bin_x<0, 1024, 8>(x, rec, n, kp, tv, pv, shm, ntiles, s);
+  }
 }
 
 template <bool kFused, int kThreads, bool kVar>
@@ -1088,7 +1108,7 @@ hipError_t launch_unstage(uint64_t n, const TableView& tv, const PartView& pv, f
   static LdsLimit lim;
   hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_unstage), shm, &lim);
   if (e != hipSuccess) return e;
-  k_unstage<<<ntiles, kUnstageThreads, shm, s>>>(pv, P, n, out, found);
+  k_unstage<<<ntiles, pv.tile <= 1024 ? 256 : kUnstageThreads, shm, s>>>(pv, P, n, out, found);
   return hipGetLastError();
 }
 
