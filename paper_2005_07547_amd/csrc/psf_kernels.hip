@@ -10,12 +10,6 @@ namespace psf {
 // ------------------------------------------------------------------ helpers
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t lane) {
-  uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
-  uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)lane);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Add a per-wave count to a device counter with one atomic from lane 0.
 __device__ __forceinline__ void wave_count(unsigned long long* ctr, bool pred) {
   const uint64_t m = __ballot(pred);
@@ -30,11 +24,17 @@ __device__ __forceinline__ uint64_t find_or_claim(const TableView& tv, uint64_t 
   const ProbeSeq ps = probe_seq(key, tv.log2_slots, tv.part_log2);
   for (uint32_t i = 0; i < tv.max_probe; ++i) {
     const uint64_t s = ps.at(i);
-    unsigned long long* kp = &tv.slots[s].key;
-    unsigned long long cur = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // A slot's key is set once, and its mirror after it: a key read from the
+    // mirror by an ordinary load is the slot's, and only one still empty
+    // there is looked at (and claimed) in the slot.
+    unsigned long long cur = tv.keys[s];
     if (cur == kEmpty) {
-      cur = atomicCAS(kp, kEmpty, (unsigned long long)key);
-      if (cur == kEmpty) tv.keys[s] = key;  // this lane claimed the slot
+      unsigned long long* kp = &tv.slots[s].key;
+      cur = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (cur == kEmpty) {
+        cur = atomicCAS(kp, kEmpty, (unsigned long long)key);
+        if (cur == kEmpty) tv.keys[s] = key;  // this lane claimed the slot
+      }
     }
     if (cur == kEmpty || cur == key) {
       *probes = i + 1;
@@ -73,10 +73,14 @@ __global__ void __launch_bounds__(256) k_keys(RecPtrs rec, uint64_t n, KeyParams
 }
 
 // ------------------------------------------------------------------ direct insert
-// One record per lane.  Lanes of a wave holding the same key elect the lowest
-// lane as leader; sums are merged in LDS; each leader claims its slot with a
-// 64-bit CAS and adds the merged count and sums with global atomics.  In a
-// weighted table the sums are of w * value and the counter adds the weights
+// One record per lane.  Lanes of a wave holding the same key elect one of
+// them as leader; sums are merged in LDS; each leader claims its slot with a
+// 64-bit CAS.  The merged counts and sums are then added with global atomics,
+// four lanes to an entry, one per word of its 16-byte accumulator: the lanes of
+// an entry share a memory request, and the device's rate of those (1.5e10/s
+// here, one a lane when each lane adds to a cell of its own) bounds the pass:
+// 1,228,800 records 224 -> 116 us.
+// In a weighted table the sums are of w * value and the counter adds the weights
 // (binary32 atomics on the counter word).  A table that keeps the luminance
 // variance also adds each sample's squared luminance (binary64) to acc_q.
 constexpr int kInsBlock = 256;
@@ -87,7 +91,10 @@ __global__ void __launch_bounds__(kInsBlock) k_insert_direct(RecPtrs rec, uint64
   __shared__ uint32_t s_cnt[kInsBlock];
   __shared__ float s_w[kInsBlock];
   __shared__ double s_q[kInsBlock];
+  __shared__ uint32_t s_slot[kInsBlock];  // an entry's slot (tables have at most 2^30), or kNoSlot
   __shared__ uint32_t s_hist[16];
+  __shared__ uint8_t s_elect[kInsBlock / 64][128];
+  constexpr uint32_t kNoSlot = ~0u;
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = lane_id();
   const uint32_t wbase = tid & ~63u;
@@ -131,16 +138,23 @@ __global__ void __launch_bounds__(kInsBlock) k_insert_direct(RecPtrs rec, uint64
   wave_count(stat_lane(tv.stats->skipped, blockIdx.x), skip);
   wave_count(stat_lane(tv.stats->coord_overflow, blockIdx.x), valid && ovf);
 
-  // elect a leader lane per distinct key
-  uint64_t pending = __ballot(valid);
+  // Elect a leader lane per distinct key: the lanes write their numbers to a
+  // small LDS table by key hash and take the lane they read back if it holds
+  // their key, again while some lane's bucket went to another key (each round
+  // settles a key in every bucket written, so it ends; with the probes'
+  // reads of the key mirror 116 -> 113 us against one round per distinct key
+  // and reads of the slots).
   uint32_t leader = 64;
-  while (pending) {
-    const uint32_t l = (uint32_t)__ffsll((unsigned long long)pending) - 1;
-    const uint64_t lk = readlane64(key, l);
-    const bool mine = valid && leader == 64 && key == lk;
-    const uint64_t m = __ballot(mine);
-    if (mine) leader = l;
-    pending &= ~m;
+  volatile uint8_t* const elect = s_elect[tid >> 6] + ((uint32_t)fmix64(key) & 127u);
+  while (__ballot(valid && leader == 64)) {
+    const bool open = valid && leader == 64;
+    if (open) *elect = (uint8_t)lane;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t w = open ? *elect : lane;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t klo = (uint32_t)__shfl((int)(uint32_t)key, (int)w);
+    const uint32_t khi = (uint32_t)__shfl((int)(uint32_t)(key >> 32), (int)w);
+    if (open && klo == (uint32_t)key && khi == (uint32_t)(key >> 32)) leader = w;
   }
   if (valid) {
     atomicAdd(&s_cnt[wbase + leader], 1u);
@@ -163,22 +177,27 @@ __global__ void __launch_bounds__(kInsBlock) k_insert_direct(RecPtrs rec, uint64
     uint32_t probes;
     slot = find_or_claim(tv, key, &probes);
     if (slot != ~0ull) {
-      Acc* a = &tv.acc[slot];
-      if (wtd)
-        atomicAdd(reinterpret_cast<float*>(&a->n), s_w[tid]);
-      else
-        atomicAdd(&a->n, cnt);
-      atomicAdd(&a->s[0], s_sum[tid][0]);
-      atomicAdd(&a->s[1], s_sum[tid][1]);
-      atomicAdd(&a->s[2], s_sum[tid][2]);
       if (tv.acc_q) atomicAdd(&tv.acc_q[slot], s_q[tid]);
       if (stats) atomicAdd(&s_hist[probes - 1 < 15 ? probes - 1 : 15], 1u);
     } else {
       atomicAdd(&tv.stats->dropped, (unsigned long long)cnt);
     }
   }
+  s_slot[tid] = slot == ~0ull ? kNoSlot : (uint32_t)slot;
+  __syncthreads();
+  const uint32_t word = tid & 3u;
+#pragma unroll
+  for (uint32_t e0 = 0; e0 < kInsBlock; e0 += kInsBlock / 4) {
+    const uint32_t e = e0 + tid / 4;
+    const uint32_t at = s_slot[e];
+    if (at == kNoSlot) continue;
+    float* acc = reinterpret_cast<float*>(tv.acc + at) + word;
+    if (word == 0 && !wtd)
+      atomicAdd(reinterpret_cast<uint32_t*>(acc), s_cnt[e]);
+    else
+      atomicAdd(acc, word == 0 ? s_w[e] : s_sum[e][word - 1]);
+  }
   if (stats) {
-    __syncthreads();
     if (tid < 16 && s_hist[tid]) atomicAdd(&tv.stats->probe_hist[tid], (unsigned long long)s_hist[tid]);
   }
 }
