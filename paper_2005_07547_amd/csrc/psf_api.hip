@@ -453,6 +453,7 @@ PSF_API psf_status psf_create_table(const psf_config* cfg, void* device_buffer, 
     t->pv.stage_q = L.stage_q ? reinterpret_cast<float*>(b + L.stage_q) : nullptr;
     t->pv.stage_n = L.stage_n ? reinterpret_cast<float4*>(b + L.stage_n) : nullptr;
     t->pv.weights = 0;
+    t->pv.state_dtype = cfg->state_dtype;
     t->pv.runs = reinterpret_cast<uint32_t*>(b + L.runs);
     t->pv.runs_t = reinterpret_cast<uint32_t*>(b + L.runs_t);
     t->pv.perm = L.perm ? reinterpret_cast<uint16_t*>(b + L.perm) : nullptr;

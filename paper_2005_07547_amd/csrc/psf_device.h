@@ -361,20 +361,27 @@ __device__ __forceinline__ float f16_to_f32(uint32_t h) {
 __device__ __forceinline__ bool state_is_f16(int32_t dtype) { return dtype == 1 || dtype == 3; }
 __device__ __forceinline__ bool state_has_residual(int32_t dtype) { return dtype >= 3; }
 
+// The three 16-bit values of a slot's first two state words.
+__device__ __forceinline__ void decode16(uint32_t w0, uint32_t w1, int32_t dtype, float& r, float& g, float& b) {
+  if (state_is_f16(dtype)) {
+    r = f16_to_f32(w0 & 0xffffu);
+    g = f16_to_f32(w0 >> 16);
+    b = f16_to_f32(w1 & 0xffffu);
+  } else {
+    r = bf16_to_f32(w0 & 0xffffu);
+    g = bf16_to_f32(w0 >> 16);
+    b = bf16_to_f32(w1 & 0xffffu);
+  }
+}
+
 // The approximant a lookup returns.
 __device__ __forceinline__ void load_state(const Slot& s, int32_t dtype, float& r, float& g, float& b) {
   if (dtype == 0) {
     r = __uint_as_float(s.L[0]);
     g = __uint_as_float(s.L[1]);
     b = __uint_as_float(s.L[2]);
-  } else if (state_is_f16(dtype)) {
-    r = f16_to_f32(s.L[0] & 0xffffu);
-    g = f16_to_f32(s.L[0] >> 16);
-    b = f16_to_f32(s.L[1] & 0xffffu);
   } else {
-    r = bf16_to_f32(s.L[0] & 0xffffu);
-    g = bf16_to_f32(s.L[0] >> 16);
-    b = bf16_to_f32(s.L[1] & 0xffffu);
+    decode16(s.L[0], s.L[1], dtype, r, g, b);
   }
 }
 

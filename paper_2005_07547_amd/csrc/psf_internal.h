@@ -28,7 +28,10 @@ struct PartView {
                                   // entry carries (with weights: the record's weight),
                                   // as a float; n = 0 marks an entry staged for lookup
                                   // only (a rejected sample).  The fused query writes
-                                  // each entry's answer {r, g, b, 0} over it.
+                                  // each entry's answer {r, g, b, 0} over it (binary32
+                                  // state) or the answer's three 16-bit values over the
+                                  // entry's key (16-bit state: half the bytes written
+                                  // and read back).
   float* stage_q;                 // per staged entry, the sum of its records' squared
                                   // luminances (tables that keep the variance; else null)
   float4* stage_n;                // per staged entry, its record's normal (SH payload
@@ -42,6 +45,7 @@ struct PartView {
   // order; kNoPos for a skipped record.  Written only when non-null (the
   // fused query of an iteration whose queries are its records).
   uint16_t* perm;
+  int32_t state_dtype;            // of the table: where and how answers are staged
   uint32_t tile;                  // records per binning tile
   uint32_t max_tiles;             // tiles per launch
   uint64_t capacity;              // records per launch
@@ -136,6 +140,8 @@ constexpr uint16_t kNoPos = 0xffffu;  // perm of a record without a valid key
 // Result of a staged entry whose key has no blended cell: a NaN pattern in
 // the red channel (real values are finite).
 constexpr uint32_t kDroppedBits = 0xffffffffu;
+// The same among 16-bit answers (the last of the four 16-bit words is else 0).
+constexpr unsigned long long kDropped16 = 0xffffull << 48;
 // Staged key of a record with a valid key but a rejected (non-finite)
 // sample: looked up, not inserted.  Valid keys never set bit 63.
 constexpr unsigned long long kLookupOnlyBit = 1ull << 63;

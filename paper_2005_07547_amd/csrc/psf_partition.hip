@@ -533,8 +533,8 @@ constexpr uint32_t kDropped = 0xffffffffu, kLookupLater = 0xfffffffeu, kAbsent =
 // One partition: blk is the block's index among the partition blocks of this
 // table (the XCD-aware order maps it to a partition).  With results (fused
 // mode only), every staged entry of the partition is overwritten with the
-// value its cell holds after the blend (kDroppedBits in place of red when
-// its key found no slot).
+// value its cell holds after the blend (kDroppedBits in place of red, or
+// kDropped16, when its key found no slot).
 template <bool kFused, int kThreads, bool kVar>
 __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& pv, uint32_t ntiles,
                                            const BlendParams& bp, uint32_t blk, bool results) {
@@ -769,11 +769,13 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
       if (old.slot.key != k) tv.keys[g] = k;
       if (results) {
         // what a lookup of the cell returns from now on
-        float v[3];
-        load_state(nw, bp.dtype, v[0], v[1], v[2]);
-        s_sum0[c] = v[0];
-        s_sum1[c] = v[1];
-        s_sum2[c] = v[2];
+        if (bp.dtype == 0) {
+          s_sum0[c] = out[0];
+          s_sum1[c] = out[1];
+          s_sum2[c] = out[2];
+        } else {
+          reinterpret_cast<unsigned long long*>(s_sum0)[c] = ((unsigned long long)enc[1] << 32) | enc[0];
+        }
       }
     } else {
       Acc a = old.acc;
@@ -789,31 +791,45 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
       }
     }
   };
-  // The value a lookup of the entry's cell returns (kDroppedBits if none),
-  // written over the entry in one 16-byte store; in the round of its cell.
-  auto answer = [&](uint32_t at, uint32_t code, uint32_t c0) {
+  // Stages the answer of the entry at `at`, the value a lookup of its cell
+  // returns: binary32 values over the entry's values, 16-bit ones over its
+  // key.  From the round's sums if in_lds (a partition of one round), else
+  // from the table.
+  auto answer = [&](uint32_t at, uint32_t code, bool in_lds) {
     if (code == kLookupLater) code = find(pv.stage_key[at] & ~kLookupOnlyBit);
-    const uint32_t i = code == kDropped ? kNone : (uint32_t)s_idx[code & kSlotBits];
-    if (i != kNone ? i - c0 >= N : c0 != 0) return;
-    float v[3] = {__uint_as_float(kDroppedBits), 0.0f, 0.0f};
-    if (i != kNone) {
-      v[0] = (float)s_sum0[i - c0];
-      v[1] = (float)s_sum1[i - c0];
-      v[2] = (float)s_sum2[i - c0];
-    } else if (code != kDropped) {
-      // a lookup-only entry whose cell this launch did not touch
-      const Slot sl = tv.slots[base + (code & kSlotBits)];
-      if (sl.c_old > 0) load_state(sl, bp.dtype, v[0], v[1], v[2]);
+    const uint32_t s = code & kSlotBits;
+    const uint32_t i = code == kDropped || !in_lds ? kNone : (uint32_t)s_idx[s];
+    Slot sl;
+    sl.c_old = 0;
+    // (with in_lds, only a lookup-only entry whose cell this launch did not
+    // touch)
+    if (code != kDropped && i == kNone) sl = tv.slots[base + s];
+    if (bp.dtype == 0) {
+      float v[3] = {__uint_as_float(kDroppedBits), 0.0f, 0.0f};
+      if (i != kNone) {
+        v[0] = (float)s_sum0[i];
+        v[1] = (float)s_sum1[i];
+        v[2] = (float)s_sum2[i];
+      } else if (sl.c_old > 0) {
+        load_state(sl, 0, v[0], v[1], v[2]);
+      }
+      pv.stage_v[at] = make_float4(v[0], v[1], v[2], 0.0f);
+    } else {
+      unsigned long long w = kDropped16;
+      if (i != kNone)
+        w = reinterpret_cast<const unsigned long long*>(s_sum0)[i];
+      else if (sl.c_old > 0)
+        w = ((unsigned long long)sl.L[1] << 32) | sl.L[0];
+      pv.stage_key[at] = w;
     }
-    pv.stage_v[at] = make_float4(v[0], v[1], v[2], 0.0f);
   };
-  auto answer_batch = [&](const uint32_t* at, const bool* ev, uint32_t c0) {
+  auto answer_batch = [&](const uint32_t* at, const bool* ev, bool in_lds) {
     unsigned long long ek[kLaterBatch];
 #pragma unroll
     for (uint32_t q = 0; q < kLaterBatch; ++q) ek[q] = pv.stage_key[at[q]];
 #pragma unroll
     for (uint32_t q = 0; q < kLaterBatch; ++q)
-      if (ev[q]) answer(at[q], find(ek[q] & ~kLookupOnlyBit), c0);
+      if (ev[q]) answer(at[q], find(ek[q] & ~kLookupOnlyBit), in_lds);
   };
 
   // The first round (the only one unless the partition is dense), with the
@@ -830,16 +846,16 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   __syncthreads();
   if (tid < cells0) write_back(tid, sl0, old0);
   for (uint32_t c = tid + kThreads; c < cells0; c += kThreads) write_back(c, s_list[c], load_old(base + s_list[c]));
-  if (results) {
+  if (results && n_touched <= N) {
     __syncthreads();
 #pragma unroll
     for (uint32_t q = 0; q < kEntryBatch; ++q)
-      if (code0[q] != kAbsent) answer(at0[q], code0[q], 0);
+      if (code0[q] != kAbsent) answer(at0[q], code0[q], true);
     rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch,
-                                            [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, 0); });
+                                            [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, true); });
   }
-  // Further rounds read the entries again (each keeps its value until the
-  // round that answers it).
+  // Further rounds read the entries again; they are answered at the end, from
+  // the cells as written back.
   for (uint32_t c0 = N; c0 < n_touched; c0 += N) {
     __syncthreads();
     clear_sums();
@@ -853,11 +869,11 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     __syncthreads();
     const uint32_t cells = n_touched - c0 < N ? n_touched - c0 : N;
     for (uint32_t c = tid; c < cells; c += kThreads) write_back(c, s_list[c], load_old(base + s_list[c]));
-    if (results) {
-      __syncthreads();
-      rr.template for_each_batch<kLaterBatch>(ch0, 0,
-                                              [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, c0); });
-    }
+  }
+  if (results && n_touched > N) {
+    __syncthreads();
+    rr.template for_each_batch<kLaterBatch>(ch0, 0,
+                                            [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, false); });
   }
 
   if (kFused && sat) atomicAdd(&s_sat, 1u);
@@ -922,13 +938,25 @@ __device__ __forceinline__ void unstage_body(const PartView& pv, uint32_t P, uin
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
   const uint64_t t0 = (uint64_t)t * pv.tile;
   const uint32_t count = pv.runs[(uint64_t)t * (P + 1) + P];
-  // the answers (r, g, b of each 16-byte entry) packed into LDS
-  const float4* src = pv.stage_v + t0;
-  for (uint32_t i = tid; i < count; i += nt) {
-    const float4 v = src[i];
-    s_res[3 * i] = v.x;
-    s_res[3 * i + 1] = v.y;
-    s_res[3 * i + 2] = v.z;
+  // the answers (r, g, b of each entry) packed into LDS
+  if (pv.state_dtype == 0) {
+    const float4* src = pv.stage_v + t0;
+    for (uint32_t i = tid; i < count; i += nt) {
+      const float4 v = src[i];
+      s_res[3 * i] = v.x;
+      s_res[3 * i + 1] = v.y;
+      s_res[3 * i + 2] = v.z;
+    }
+  } else {
+    const unsigned long long* src = pv.stage_key + t0;
+    for (uint32_t i = tid; i < count; i += nt) {
+      const unsigned long long w = src[i];
+      float r, g, b;
+      decode16((uint32_t)w, (uint32_t)(w >> 32), pv.state_dtype, r, g, b);
+      s_res[3 * i] = w == kDropped16 ? __uint_as_float(kDroppedBits) : r;
+      s_res[3 * i + 1] = g;
+      s_res[3 * i + 2] = b;
+    }
   }
   __syncthreads();
   const uint64_t end = t0 + pv.tile < n ? t0 + pv.tile : n;

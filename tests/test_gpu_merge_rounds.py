@@ -54,3 +54,28 @@ def test_dense_partitions_match_the_oracle(kind, part_log2, fused):
         m = o["L"][0] * 0.25 + o["L"][1] * 0.5 + o["L"][2] * 0.25
         assert np.array_equal(keys, o_keys)
         assert np.all(np.abs(var - o_var) <= RTOL * (o_var + m * m) + 1e-30)
+
+
+@pytest.mark.parametrize("dtype", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("log2_slots,part_log2", [(13, 12), (13, 9), (16, 11)])
+def test_fused_answers_equal_a_lookup_in_every_state_format(dtype, log2_slots, part_log2):
+    """Answers staged as 16-bit words (or binary32 values), by partitions of
+    one round and of several, equal those of a separate lookup bit for bit:
+    hits, rejected samples, rejected vertices and keys that found no slot."""
+    from paper_2005_07547_amd import psf
+    from synth import workloads as W
+    wl = W.tiny(alpha_mode=W.ALPHA_PAPER)
+    sc = W.make_scene(wl)
+    # 4 probes: in 2^13 slots many keys find none
+    t = psf.Table(**dict(wl["table"], log2_slots=log2_slots, part_log2=part_log2, max_probe=4, state_dtype=dtype))
+    for it in range(3):
+        rec = dict(sc.generate(wl["gen"], it))
+        rec["rough"] = None
+        rec["g"][3::17] = np.inf
+        rec["nx"][1::29] = np.nan
+        d = to_device({k: (v[:8191 - it] if v is not None else None) for k, v in rec.items()})
+        out, found = t.iterate(d)
+        again, hit = t.query(d)
+        assert np.array_equal(found.cpu().numpy(), hit.cpu().numpy())
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), again.cpu().numpy().view(np.uint32))
+    assert log2_slots == 16 or t.stats()["dropped"] > 0
