@@ -179,7 +179,7 @@ hipError_t launch_batch(const BatchSession* d_sessions, const uint32_t* d_begins
                         uint32_t stride, const BatchSession* h_sessions, uint32_t k, hipStream_t s);
 // Threads of a batch query block: the lookup of kQueryBlock queries, or the
 // unstage of one fused session's tile (as wide as the single-table unstage).
-constexpr uint32_t kQueryBlock = 512;
+constexpr uint32_t kQueryBlock = 1024;
 // Path sampler (the public structures, device copies in the kernels).
 using PathPrim = psf_prim;
 using PathCamera = psf_camera;

@@ -917,7 +917,8 @@ k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp, int32_t resu
 // four consecutive records at a time (8-byte perm loads, 16-byte stores when
 // the output rows are 16-byte aligned; non-temporal, since no kernel of the
 // iteration reads the answers again).
-constexpr uint32_t kUnstageThreads = 512;  // (256 for the 1024-record tiles of small launches)
+constexpr uint32_t kUnstageThreads = 1024;
+static uint32_t unstage_threads(uint32_t tile) { return tile <= 4096 ? tile / 4 : tile == 6144 ? 768 : 1024; }
 
 __device__ __forceinline__ void unstage_one(const float* s_res, uint32_t count, uint32_t pos, float& r,
                                             float& g, float& b, uint8_t& f) {
@@ -1136,7 +1137,7 @@ hipError_t launch_unstage(uint64_t n, const TableView& tv, const PartView& pv, f
   static LdsLimit lim;
   hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_unstage), shm, &lim);
   if (e != hipSuccess) return e;
-  k_unstage<<<ntiles, pv.tile <= 1024 ? 256 : kUnstageThreads, shm, s>>>(pv, P, n, out, found);
+  k_unstage<<<ntiles, unstage_threads(pv.tile), shm, s>>>(pv, P, n, out, found);
   return hipGetLastError();
 }
 
