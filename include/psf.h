@@ -195,10 +195,12 @@ typedef struct psf_config {
   uint32_t flags;            /* PSF_FLAG_* */
   int32_t insert_mode;       /* PSF_INSERT_* */
   uint32_t part_log2;        /* partitioned insert: log2 slots per partition
-                                (0 = default: 11, or 12 for tables of 2^25
+                                (0 = default: 11, or 12 for tables of 2^21
                                 slots or more; else 8..12.  With
-                                PSF_FLAG_TRACK_VARIANCE or weighted = 1:
-                                default 11, at most 11).  A table of
+                                PSF_FLAG_TRACK_VARIANCE or weighted = 1 at
+                                most 11 (default 12 for 2^21 to 2^25
+                                slots); with the SH payload the default
+                                stays 11 up to 2^24 slots).  A table of
                                 more than 16384 partitions takes the direct
                                 strategy. */
   uint64_t max_batch;        /* partitioned insert: records binned per launch

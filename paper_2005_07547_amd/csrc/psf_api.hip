@@ -112,7 +112,7 @@ hipError_t timed(psf_table* t, int kind, hipStream_t s, F&& launch) {
   return hipSuccess;
 }
 
-constexpr uint32_t kDefaultPartLog2 = 11;
+constexpr uint32_t kDefaultPartLog2 = 11, kWidePartSlots = 21;
 constexpr uint32_t kDefaultBinPer = 8;
 constexpr uint64_t kDefaultBatch = 1ull << 22;
 // Partitions of a partitioned table: at most 2^14 (beyond, the merge's
@@ -186,20 +186,23 @@ uint32_t bin_per_of(const psf_config& c) {
 Layout layout_of(const psf_config& c) {
   Layout L;
   const uint64_t S = 1ull << c.log2_slots;
-  // default partition width: 2^11 slots, wider for tables that would
-  // otherwise exceed the binning pass's partition count
-  // (at most 2^11 with the variance or weights; at 2^10 a frame of 3,686,400
-  // weighted records merged in 154 us, at 2^11, with runs twice as long, in
-  // 143)
+  // default partition width: 2^11 slots, 2^12 for RGB tables of 2^21 slots and
+  // more, whose 512 and more partitions still fill the device (runs twice as
+  // long; us a frame at 2^11 and 2^12: 3,686,400 records into 2^22 slots 178
+  // and 160, weighted 238 and 213; 2,073,600 into 2^21 108 and 93; but 921,600
+  // into 2^20 52 and 57).  Weighted and variance tables keep 2^11 past 2^25
+  // slots, where the width decides whether a table is partitioned, and take no
+  // explicit 2^12.
   const bool extra = (c.flags & PSF_FLAG_TRACK_VARIANCE) || c.weighted;
+  const bool sh = c.payload == PSF_PAYLOAD_SH2_YCOCG;
   const uint32_t widest = extra ? 11u : 12u;
   uint32_t def = kDefaultPartLog2;
   while (def < widest && c.log2_slots > def && (1ull << (c.log2_slots - def)) > kDefaultPartitions) ++def;
+  if (!sh && c.log2_slots >= kWidePartSlots && (!extra || c.log2_slots <= 25)) def = 12;
   L.part_log2 = c.part_log2 ? c.part_log2 : def;
   if (L.part_log2 > c.log2_slots) L.part_log2 = c.log2_slots;
   const uint64_t P = 1ull << (c.log2_slots - L.part_log2);
   L.part = c.insert_mode != PSF_INSERT_DIRECT && P <= kMaxPartitions;
-  const bool sh = c.payload == PSF_PAYLOAD_SH2_YCOCG;
   size_t off = 0;
   L.stats = off;
   off = align_up(off + sizeof(psf::DevStats), 256);
