@@ -376,12 +376,14 @@ __device__ __forceinline__ void decode16(uint32_t w0, uint32_t w1, int32_t dtype
 
 // The approximant a lookup returns.
 __device__ __forceinline__ void load_state(const Slot& s, int32_t dtype, float& r, float& g, float& b) {
+  // (words first: selected by address, a slot held in registers would go
+  // through scratch memory)
+  const uint32_t w0 = s.L[0], w1 = s.L[1], w2 = s.L[2];
+  decode16(w0, w1, dtype, r, g, b);
   if (dtype == 0) {
-    r = __uint_as_float(s.L[0]);
-    g = __uint_as_float(s.L[1]);
-    b = __uint_as_float(s.L[2]);
-  } else {
-    decode16(s.L[0], s.L[1], dtype, r, g, b);
+    r = __uint_as_float(w0);
+    g = __uint_as_float(w1);
+    b = __uint_as_float(w2);
   }
 }
 
