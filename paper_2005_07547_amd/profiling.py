@@ -29,7 +29,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ("csrc/psf_device.h", "csrc/psf_internal.h", "csrc/psf_kernels.hip",
-           "csrc/psf_partition.hip")
+           "csrc/psf_partition.hip", "csrc/psf_runs.h")
 COPY_BYTES = 1 << 30
 
 
