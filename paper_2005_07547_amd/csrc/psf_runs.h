@@ -51,8 +51,11 @@ struct RunReader {
 
   __device__ __forceinline__ RunReader(const PartView& v, uint32_t part, uint32_t nparts, uint32_t ntiles)
       : pv(v), p(part), P(nparts), lane(__lane_id()) {
-    // (a multiple of 4 tiles, so that a lane's runs are one 16-byte load)
-    const uint32_t per_wave = ((ntiles + kWaves - 1) / kWaves + 3u) & ~3u;
+    // (in a transposed table a multiple of 4 tiles, so that a lane's runs are
+    // one 16-byte load; read in place, any number: the few tiles of a small
+    // launch go to as many waves)
+    uint32_t per_wave = (ntiles + kWaves - 1) / kWaves;
+    if (pv.runs_t) per_wave = (per_wave + 3u) & ~3u;
     w_lo = (threadIdx.x >> 6) * per_wave;
     w_hi = (w_lo + per_wave < ntiles) ? w_lo + per_wave : ntiles;
     const uint32_t stride = (pv.max_tiles + 3u) & ~3u;
