@@ -444,8 +444,7 @@ psf_status psf_export_sh_cells(psf_table* t, uint64_t* keys, uint32_t* c_old, fl
  * result equals the same session run alone through psf_iterate.  Sessions
  * that cannot join the batch (direct insert strategy, samples pending from
  * psf_insert_samples, n above the table's max_batch, a binning width
- * different from the first batchable session's, partitions wider than both
- * 2^11 slots and the narrowest batchable session's) run through psf_iterate
+ * different from the first batchable session's) run through psf_iterate
  * first, on the same stream.  d_out_rgb (3*nq floats, SoA) and d_out_found
  * (nullable) as in psf_query; queries equal to the records (the same
  * arrays) are answered by the merge pass, as in psf_iterate. */
