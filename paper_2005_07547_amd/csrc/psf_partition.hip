@@ -1307,7 +1307,6 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   size_t lds_b = 0, lds_m = 0, lds_q = 0;
   uint32_t x = 0, part_log2 = 0;  // what any session's records carry; the widest partitions
   bool var = false;
-  const uint32_t per = h_ss[0].pv.tile / 512;
   for (uint32_t i = 0; i < k; ++i) {
     const BatchSession& S = h_ss[i];
     if (h_begins[i] != S.tile_begin || h_begins[stride + i] != S.part_begin ||
@@ -1342,9 +1341,14 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   const uint32_t* bg_part = d_begins + stride;
   const uint32_t* bg_qblk = d_begins + 2 * stride;
   const uint32_t* bg_trans = d_begins + 3 * stride;
-  hipError_t e = per == 8    ? launch_bin_batch_x<1024, 4>(x, d_ss, bg_tile, k, tiles, lds_b, s)
-                  : per == 12 ? launch_bin_batch_x<512, 12>(x, d_ss, bg_tile, k, tiles, lds_b, s)
-                              : launch_bin_batch_x<1024, 8>(x, d_ss, bg_tile, k, tiles, lds_b, s);
+  hipError_t e;
+  switch (h_ss[0].pv.tile) {
+    case 1024: e = launch_bin_batch_x<1024, 1>(x, d_ss, bg_tile, k, tiles, lds_b, s); break;
+    case 2048: e = launch_bin_batch_x<1024, 2>(x, d_ss, bg_tile, k, tiles, lds_b, s); break;
+    case 4096: e = launch_bin_batch_x<1024, 4>(x, d_ss, bg_tile, k, tiles, lds_b, s); break;
+    case 6144: e = launch_bin_batch_x<512, 12>(x, d_ss, bg_tile, k, tiles, lds_b, s); break;
+    default: e = launch_bin_batch_x<1024, 8>(x, d_ss, bg_tile, k, tiles, lds_b, s); break;
+  }
   if (e != hipSuccess) return e;
   e = lds_limit(reinterpret_cast<const void*>(&k_query_batch), lds_q, &lim_q);
   if (e != hipSuccess) return e;
