@@ -56,12 +56,16 @@ def kernel_resources(lib: str = OUT) -> dict:
 
 
 def check_resources(kernels: dict) -> None:
-    """The binning kernels' dynamic LDS holds 16-byte values, so it has to
-    start at a multiple of 16 behind the static part."""
+    """The binning kernels keep a thread's records in registers across the
+    sort.  One instantiation that the compiler made to spill to scratch lost a
+    row of every tile, so none may; and their dynamic LDS holds 16-byte values,
+    so it has to start at a multiple of 16 behind the static part."""
     binning = {n: k for n, k in kernels.items() if "k_bin" in n}
     if not binning:
         raise RuntimeError("no binning kernels in the library")
     for name, k in binning.items():
+        if k["private_segment_fixed_size"] or k["vgpr_spill_count"]:
+            raise RuntimeError(f"{name} spills registers to scratch")
         if k["group_segment_fixed_size"] % 16:
             raise RuntimeError(f"{name}: dynamic LDS starts at {k['group_segment_fixed_size']}, not a multiple of 16")
 
