@@ -199,8 +199,10 @@ typedef struct psf_config {
                                 slots or more; else 8..12.  With
                                 PSF_FLAG_TRACK_VARIANCE or weighted = 1 at
                                 most 11 (default 12 for 2^21 to 2^25
-                                slots); with the SH payload the default
-                                stays 11 up to 2^24 slots).  A table of
+                                slots; with max_batch above 5/4 of the
+                                slots 11, and 10 below 2^21); with the SH
+                                payload the default stays 11 up to 2^24
+                                slots).  A table of
                                 more than 16384 partitions takes the direct
                                 strategy. */
   uint64_t max_batch;        /* partitioned insert: records binned per launch

@@ -186,19 +186,24 @@ uint32_t bin_per_of(const psf_config& c) {
 Layout layout_of(const psf_config& c) {
   Layout L;
   const uint64_t S = 1ull << c.log2_slots;
+  const uint64_t tile = psf::bin_tile(bin_per_of(c));
+  L.cap = ((c.max_batch ? c.max_batch : kDefaultBatch) + tile - 1) / tile * tile;
   // default partition width: 2^11 slots, 2^12 for RGB tables of 2^21 slots and
   // more, whose 512 and more partitions still fill the device (runs twice as
   // long; us a frame at 2^11 and 2^12: 3,686,400 records into 2^22 slots 178
   // and 160, weighted 238 and 213; 2,073,600 into 2^21 108 and 93; but 921,600
   // into 2^20 52 and 57).  Weighted and variance tables keep 2^11 past 2^25
   // slots, where the width decides whether a table is partitioned, and take no
-  // explicit 2^12.
+  // explicit 2^12.  Where their launches can be dense, the sums of every slot
+  // have to fit: 2^11, and 2^10 below 2^21 slots (2^16 slots, 1,048,576 weighted
+  // records: 256 us at 2^10, 373 at 2^11; 2^22 slots, 8,388,608: 504 and 490).
   const bool extra = (c.flags & PSF_FLAG_TRACK_VARIANCE) || c.weighted;
   const bool sh = c.payload == PSF_PAYLOAD_SH2_YCOCG;
+  const bool crowded = extra && !sh && psf::dense_records(L.cap, S);
   const uint32_t widest = extra ? 11u : 12u;
-  uint32_t def = kDefaultPartLog2;
+  uint32_t def = crowded && c.log2_slots < kWidePartSlots ? kDefaultPartLog2 - 1 : kDefaultPartLog2;
   while (def < widest && c.log2_slots > def && (1ull << (c.log2_slots - def)) > kDefaultPartitions) ++def;
-  if (!sh && c.log2_slots >= kWidePartSlots && (!extra || c.log2_slots <= 25)) def = 12;
+  if (!sh && c.log2_slots >= kWidePartSlots && (!extra || (c.log2_slots <= 25 && !crowded))) def = 12;
   L.part_log2 = c.part_log2 ? c.part_log2 : def;
   if (L.part_log2 > c.log2_slots) L.part_log2 = c.log2_slots;
   const uint64_t P = 1ull << (c.log2_slots - L.part_log2);
@@ -232,10 +237,7 @@ Layout layout_of(const psf_config& c) {
     }
   }
   if (L.part) {
-    const uint64_t tile = psf::bin_tile(bin_per_of(c));
-    L.cap = c.max_batch ? c.max_batch : kDefaultBatch;
-    L.tiles = (uint32_t)((L.cap + tile - 1) / tile);
-    L.cap = (uint64_t)L.tiles * tile;
+    L.tiles = (uint32_t)(L.cap / tile);
     // rows of the offset tables: also the smaller tiles of a small launch
     const uint64_t small = (L.cap + 1023) / 1024;
     if (!c.bin_per) L.tiles = (uint32_t)std::max<uint64_t>(L.tiles, std::min<uint64_t>(small, psf::kSmallTiles));
@@ -330,6 +332,7 @@ psf_status do_insert(psf_table* t, const psf::RecPtrs& rp, uint64_t n, hipStream
       pv.perm = nullptr;
       pv.weights = sub.weight != nullptr;
       pv.tile = tile_for(t, m);
+      pv.dense = psf::dense_launch(m, t->tv);
       const uint32_t nt = (uint32_t)((m + pv.tile - 1) / pv.tile);
       if (!transpose_runs(t, nt)) pv.runs_t = nullptr;
       e = timed(t, PSF_K_BIN, s, [&] { return psf::launch_bin(sub, m, t->kp, t->tv, pv, s); });
@@ -456,6 +459,7 @@ PSF_API psf_status psf_create_table(const psf_config* cfg, void* device_buffer, 
     t->pv.stage_q = L.stage_q ? reinterpret_cast<float*>(b + L.stage_q) : nullptr;
     t->pv.stage_n = L.stage_n ? reinterpret_cast<float4*>(b + L.stage_n) : nullptr;
     t->pv.weights = 0;
+    t->pv.dense = 0;
     t->pv.state_dtype = cfg->state_dtype;
     t->pv.runs = reinterpret_cast<uint32_t*>(b + L.runs);
     t->pv.runs_t = reinterpret_cast<uint32_t*>(b + L.runs_t);
@@ -557,6 +561,7 @@ PSF_API psf_status psf_iterate(psf_table* t, const psf_records* rec, uint64_t n,
     if (!fq) pv.perm = nullptr;
     pv.weights = rp.weight != nullptr;
     pv.tile = tile_for(t, n);
+    pv.dense = psf::dense_launch(n, t->tv);
     const uint32_t nt = (uint32_t)((n + pv.tile - 1) / pv.tile);
     if (!transpose_runs(t, nt)) pv.runs_t = nullptr;
     hipError_t e = timed(t, PSF_K_BIN, s, [&] { return psf::launch_bin(rp, n, t->kp, t->tv, pv, s); });
@@ -1055,6 +1060,7 @@ PSF_API psf_status psf_iterate_batch(psf_batch* b, const psf_session* sessions, 
     if (!d.fused_query) d.pv.perm = nullptr;
     d.pv.weights = d.rec.weight != nullptr;
     d.pv.tile = tile;
+    d.pv.dense = psf::dense_launch(ss.n, t->tv);
     d.tile_begin = tiles;
     d.ntiles = (uint32_t)((ss.n + tile - 1) / tile);
     d.part_begin = parts;

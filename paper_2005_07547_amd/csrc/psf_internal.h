@@ -47,6 +47,7 @@ struct PartView {
   uint16_t* perm;
   int32_t state_dtype;            // of the table: where and how answers are staged
   uint32_t tile;                  // records per binning tile
+  uint32_t dense;                 // this launch has many records a slot (dense_launch)
   uint32_t max_tiles;             // tiles per launch
   uint64_t capacity;              // records per launch
 };
@@ -149,6 +150,11 @@ bool bin_per_ok(uint32_t per);          // supported records per thread of the b
 uint32_t bin_tile(uint32_t per);        // records per binning tile
 constexpr uint32_t kSmallTiles = 512;    // most tiles of a launch that takes smaller ones
 uint32_t launch_tile(uint64_t n, uint32_t nparts);  // records per tile at the default width
+// Whether a launch of n records sums every slot of a partition in one sweep,
+// or (the default) the touched ones in rounds; and whether its records are
+// that many, whatever its partitions.
+bool dense_launch(uint64_t n, const TableView& tv);
+bool dense_records(uint64_t n, uint64_t slots);
 uint32_t update_grid(uint64_t nslots);  // blocks of the streaming update
 
 // One session of a batched iteration (device copy read by the batch kernels).

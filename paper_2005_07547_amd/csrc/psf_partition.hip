@@ -517,11 +517,17 @@ __global__ void __launch_bounds__(kTransposeThreads) k_transpose_runs(PartView p
 // records into 2^22 slots: 98 -> 82 us; 10,368,000 into 2^24: 336 -> 278 us
 // (266 with the answers of its 16-bit state staged in half the bytes).
 // (32 wavefronts need 64 registers and spill 37 more: 176 us.)  A partition
-// with more touched cells takes further rounds over its entries.
+// with more touched cells takes further rounds over its entries, each of them
+// as long as the first; dense_launch tells the launches that would.
 __host__ __device__ constexpr uint32_t merge_cells(uint32_t slots, bool extra) {
   return extra ? slots / 4 : slots / 16 * 5;
 }
-__host__ __device__ constexpr size_t merge_lds_bytes(uint32_t slots, bool extra) {
+// Dense launches (many records a slot) keep sums for every slot instead: an
+// entry is then added as soon as its slot is found, its key and value read
+// once, and no partition needs a second round (38 bytes a slot, 46 with the
+// further sum; 16 wavefronts a CU).
+__host__ __device__ constexpr size_t merge_lds_bytes(uint32_t slots, bool extra, bool dense) {
+  if (dense) return (size_t)slots * (8 + 24 + 4 + 2 + (extra ? 8 : 0));
   return (size_t)slots * (8 + 2) + (size_t)merge_cells(slots, extra) * (24 + 4 + 2 + (extra ? 8 : 0));
 }
 
@@ -540,7 +546,7 @@ constexpr uint32_t kDropped = 0xffffffffu, kLookupLater = 0xfffffffeu, kAbsent =
 // mode only), every staged entry of the partition is overwritten with the
 // value its cell holds after the blend (kDroppedBits in place of red, or
 // kDropped16, when its key found no slot).
-template <bool kFused, int kThreads, bool kVar>
+template <bool kFused, int kThreads, bool kVar, bool kDense>
 __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& pv, uint32_t ntiles,
                                            const BlendParams& bp, uint32_t blk, bool results) {
   // key[B] | sum[3][N] (binary64: LDS f64 atomics are both faster than f32
@@ -552,6 +558,8 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   // cnt is then unused; every entry is one record) | cnt[N] | place of a
   // slot in the list of touched slots[B] (16-bit) | the round's part of that
   // list[N] (16-bit).  After the blend the sums hold the cells' new values.
+  // (kDense: N = B, the sums are indexed by slot, a slot with a count is
+  // touched, in a weighted table too, and there are no places, only the list.)
   extern __shared__ unsigned long long s_dyn[];
   __shared__ uint32_t s_dropped, s_nlist, s_sat;
   __shared__ uint32_t s_hist[16];
@@ -563,22 +571,22 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   const uint64_t base = (uint64_t)p << tv.part_log2;
   const bool stats = (tv.flags & 1u) != 0;
   const bool wtd = weighted(tv);
-  const uint32_t N = merge_cells(B, kVar || wtd);
+  const uint32_t N = kDense ? B : merge_cells(B, kVar || wtd);
   unsigned long long* s_key = s_dyn;
   double* s_sum0 = reinterpret_cast<double*>(s_key + B);
   double* s_sum1 = s_sum0 + N;
   double* s_sum2 = s_sum1 + N;
   double* s_sumx = s_sum2 + N;  // only with tv.var or wtd
   uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_sumx + ((kVar || wtd) ? N : 0u));
-  uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_cnt + N);
-  uint16_t* s_list = s_idx + B;
+  uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_cnt + N);  // not kDense
+  uint16_t* s_list = kDense ? s_idx : s_idx + B;
   constexpr uint32_t kNone = 0xffffu;
   if (!kFused) results = false;
 
   // keys first, then the first runs, then the keys of the wave's first batch
   // of entries: all in flight together, before the key table is built
   const RunReader<kWaves> rr(pv, p, P, ntiles);
-  constexpr uint32_t kKeysPerThread = 6;  // (the launch has at least B / 6 threads)
+  constexpr uint32_t kKeysPerThread = kDense ? 4 : 6;  // (the launch has at least B / 4 or B / 6 threads)
   unsigned long long kk[kKeysPerThread];
 #pragma unroll
   for (uint32_t j = 0; j < kKeysPerThread; ++j) {
@@ -589,6 +597,15 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   uint32_t at0[kEntryBatch], code0[kEntryBatch];
   unsigned long long ek0[kEntryBatch];
   bool ev0[kEntryBatch];
+  float4 v0[kEntryBatch];
+  float q0[kEntryBatch];  // variance tables: the entries' squared-luminance sums
+  auto load_values = [&]() {
+#pragma unroll
+    for (uint32_t q = 0; q < kEntryBatch; ++q) {
+      v0[q] = pv.stage_v[at0[q]];
+      q0[q] = kVar ? pv.stage_q[at0[q]] : 0.0f;
+    }
+  };
 #pragma unroll
   for (uint32_t q = 0; q < kEntryBatch; ++q) ev0[q] = false;
   const bool any = rr.w_lo < rr.w_hi;  // the wave has tiles (wave-uniform)
@@ -597,6 +614,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     rr.template batch_of<kEntryBatch>(ch0, 0, at0, ev0);
 #pragma unroll
     for (uint32_t q = 0; q < kEntryBatch; ++q) ek0[q] = pv.stage_key[at0[q]];
+    if (kDense) load_values();
   }
   auto clear_sums = [&]() {
     for (uint32_t c = tid; c < N; c += kThreads) {
@@ -611,7 +629,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     const uint32_t s = tid + j * kThreads;
     if (s < B) {
       s_key[s] = kk[j];
-      s_idx[s] = (uint16_t)kNone;
+      if (!kDense) s_idx[s] = (uint16_t)kNone;
     }
   }
   if (tid == 0) s_dropped = s_nlist = s_sat = 0;
@@ -626,7 +644,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
       unsigned long long cur = s_key[s];
       if (cur == kEmpty) cur = atomicCAS(&s_key[s], kEmpty, key);
       if (cur == kEmpty || cur == key) {
-        s_idx[s] = 0;
+        if (!kDense) s_idx[s] = 0;
         return s | ((i < 15 ? i : 15u) << kProbesShift);
       }
     }
@@ -646,44 +664,6 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
 #pragma unroll
   for (uint32_t q = 0; q < kEntryBatch; ++q)
     code0[q] = !ev0[q] ? kAbsent : (ek0[q] & kLookupOnlyBit) ? kLookupLater : claim(ek0[q]);
-  // the first batch's values arrive while the touched slots are listed
-  float4 v0[kEntryBatch];
-  float q0[kEntryBatch];  // variance tables: the entries' squared-luminance sums
-  if (any) {
-#pragma unroll
-    for (uint32_t q = 0; q < kEntryBatch; ++q) {
-      v0[q] = pv.stage_v[at0[q]];
-      q0[q] = kVar ? pv.stage_q[at0[q]] : 0.0f;
-    }
-  }
-  rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch, [&](const uint32_t* at, const bool* ev) {
-    unsigned long long ek[kLaterBatch];
-#pragma unroll
-    for (uint32_t q = 0; q < kLaterBatch; ++q) ek[q] = pv.stage_key[at[q]];
-#pragma unroll
-    for (uint32_t q = 0; q < kLaterBatch; ++q)
-      if (ev[q] && !(ek[q] & kLookupOnlyBit)) claim(ek[q]);
-  });
-  __syncthreads();
-
-  // List the touched slots (about one in eight, scattered), so that the sums
-  // are kept for them alone and the write-back runs on full waves.
-  for (uint32_t s0 = 0; s0 < B; s0 += kThreads) {
-    const uint32_t s = s0 + tid;
-    const bool hit = s < B && s_idx[s] != kNone;
-    const unsigned long long m = __ballot(hit);
-    uint32_t at = 0;
-    if (lane == 0 && m) at = atomicAdd(&s_nlist, (uint32_t)__popcll(m));
-    at = (uint32_t)__shfl((int)at, 0);
-    if (hit) {
-      at += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-      s_idx[s] = (uint16_t)at;
-      if (at < N) s_list[at] = (uint16_t)s;
-    }
-  }
-  __syncthreads();
-  const uint32_t n_touched = s_nlist;
-  bool sat = false;
 
   // Adds an entry to its cell's sums if the cell is in the round from c0 on.
   auto add = [&](uint32_t code, const float4& v, float qv, uint32_t c0) {
@@ -692,31 +672,19 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
       if (c0 == 0) atomicAdd(&s_dropped, recs);
       return;
     }
-    const uint32_t c = (uint32_t)s_idx[code & kSlotBits] - c0;
+    const uint32_t c = kDense ? code & kSlotBits : (uint32_t)s_idx[code & kSlotBits] - c0;
     if (c >= N) return;
     if (stats) atomicAdd(&s_hist[code >> kProbesShift], recs);
-    if (wtd)
+    if (wtd) {
       atomicAdd(&s_sumx[c], (double)v.w);
-    else
+      if (kDense) s_cnt[c] = 1u;
+    } else {
       atomicAdd(&s_cnt[c], (uint32_t)v.w);
+    }
     atomicAdd(&s_sum0[c], (double)v.x);
     atomicAdd(&s_sum1[c], (double)v.y);
     atomicAdd(&s_sum2[c], (double)v.z);
     if (kVar) atomicAdd(&s_sumx[c], (double)qv);
-  };
-  auto add_batch = [&](const uint32_t* at, const bool* ev, uint32_t c0) {
-    unsigned long long ek[kLaterBatch];
-    float4 v[kLaterBatch];
-    float qv[kLaterBatch];
-#pragma unroll
-    for (uint32_t q = 0; q < kLaterBatch; ++q) {
-      ek[q] = pv.stage_key[at[q]];
-      v[q] = pv.stage_v[at[q]];
-      qv[q] = kVar ? pv.stage_q[at[q]] : 0.0f;
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < kLaterBatch; ++q)
-      if (ev[q] && !(ek[q] & kLookupOnlyBit)) add(find(ek[q]), v[q], qv[q], c0);
   };
   // What the table holds of a touched slot before this launch.
   struct Old {
@@ -737,6 +705,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     }
     return o;
   };
+  bool sat = false;
   // Writes touched cell c of the round back (slot s of the partition).
   auto write_back = [&](uint32_t c, uint32_t s, const Old& old) {
     const uint64_t g = base + s;
@@ -803,7 +772,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   auto answer = [&](uint32_t at, uint32_t code, bool in_lds) {
     if (code == kLookupLater) code = find(pv.stage_key[at] & ~kLookupOnlyBit);
     const uint32_t s = code & kSlotBits;
-    const uint32_t i = code == kDropped || !in_lds ? kNone : (uint32_t)s_idx[s];
+    const uint32_t i = code == kDropped || !in_lds ? kNone : !kDense ? (uint32_t)s_idx[s] : s_cnt[s] ? s : kNone;
     Slot sl;
     sl.c_old = 0;
     // (with in_lds, only a lookup-only entry whose cell this launch did not
@@ -827,6 +796,139 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
         w = ((unsigned long long)sl.L[1] << 32) | sl.L[0];
       pv.stage_key[at] = w;
     }
+  };
+  // Counters of the partition, once every thread is done with it.
+  auto finish = [&](uint32_t n_touched) {
+    if (kFused && sat) atomicAdd(&s_sat, 1u);
+    __syncthreads();
+    if (tid == 0) {
+      if (s_dropped) atomicAdd(&tv.stats->dropped, (unsigned long long)s_dropped);
+      if (kFused) {
+        if (s_sat) atomicAdd(&tv.stats->saturated, (unsigned long long)s_sat);
+        BlockTouch* bt = &tv.touch[blk];
+        bt->last = n_touched;
+        bt->total += n_touched;
+      }
+    }
+    if (stats && tid < 16 && s_hist[tid])
+      atomicAdd(&tv.stats->probe_hist[tid], (unsigned long long)s_hist[tid]);
+  };
+  if constexpr (kDense) {
+    // one sweep: every entry is added as it is read; the places of a wave's
+    // second batch are kept beside those of its first for the answers
+    uint32_t at1[kEntryBatch], code1[kEntryBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kEntryBatch; ++q) {
+      if (code0[q] != kAbsent && code0[q] != kLookupLater) add(code0[q], v0[q], q0[q], 0);
+      code1[q] = kAbsent;
+    }
+    uint32_t nb = 0;
+    rr.template for_each_batch<kEntryBatch>(ch0, 64 * kEntryBatch, [&](const uint32_t* at, const bool* ev) {
+      unsigned long long ek[kEntryBatch];
+      float4 v[kEntryBatch];
+      float qv[kEntryBatch];
+#pragma unroll
+      for (uint32_t q = 0; q < kEntryBatch; ++q) {
+        ek[q] = pv.stage_key[at[q]];
+        v[q] = pv.stage_v[at[q]];
+        qv[q] = kVar ? pv.stage_q[at[q]] : 0.0f;
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < kEntryBatch; ++q) {
+        const uint32_t code = !ev[q] ? kAbsent : (ek[q] & kLookupOnlyBit) ? kLookupLater : claim(ek[q]);
+        if (code != kAbsent && code != kLookupLater) add(code, v[q], qv[q], 0);
+        if (nb == 0) {
+          at1[q] = at[q];
+          code1[q] = code;
+        }
+      }
+      ++nb;
+    });
+    __syncthreads();
+    for (uint32_t s0 = 0; s0 < B; s0 += kThreads) {
+      const uint32_t s = s0 + tid;
+      const bool hit = s < B && s_cnt[s] != 0u;
+      const unsigned long long m = __ballot(hit);
+      uint32_t at = 0;
+      if (lane == 0 && m) at = atomicAdd(&s_nlist, (uint32_t)__popcll(m));
+      at = (uint32_t)__shfl((int)at, 0);
+      if (hit)
+        s_list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+            (uint16_t)s;
+    }
+    __syncthreads();
+    // two cells a thread at a time, their old slots in one round trip
+    const uint32_t n_touched = s_nlist;
+    for (uint32_t i = tid; i < n_touched; i += 2 * kThreads) {
+      const bool two = i + kThreads < n_touched;
+      const uint32_t sa = s_list[i], sb = s_list[two ? i + kThreads : i];
+      const Old oa = load_old(base + sa), ob = load_old(base + sb);
+      write_back(sa, sa, oa);
+      if (two) write_back(sb, sb, ob);
+    }
+    if (results) {
+      __syncthreads();
+#pragma unroll
+      for (uint32_t q = 0; q < kEntryBatch; ++q) {
+        if (code0[q] != kAbsent) answer(at0[q], code0[q], true);
+        if (code1[q] != kAbsent) answer(at1[q], code1[q], true);
+      }
+      nb = 0;
+      rr.template for_each_batch<kEntryBatch>(ch0, 64 * kEntryBatch, [&](const uint32_t* at, const bool* ev) {
+        if (nb++ == 0) return;
+        unsigned long long ek[kEntryBatch];
+#pragma unroll
+        for (uint32_t q = 0; q < kEntryBatch; ++q) ek[q] = pv.stage_key[at[q]];
+#pragma unroll
+        for (uint32_t q = 0; q < kEntryBatch; ++q)
+          if (ev[q]) answer(at[q], find(ek[q] & ~kLookupOnlyBit), true);
+      });
+    }
+    finish(n_touched);
+    return;
+  }
+  // the first batch's values arrive while the touched slots are listed
+  if (any) load_values();
+  rr.template for_each_batch<kLaterBatch>(ch0, 64 * kEntryBatch, [&](const uint32_t* at, const bool* ev) {
+    unsigned long long ek[kLaterBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q) ek[q] = pv.stage_key[at[q]];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q)
+      if (ev[q] && !(ek[q] & kLookupOnlyBit)) claim(ek[q]);
+  });
+  __syncthreads();
+
+  // List the touched slots (about one in eight, scattered), so that the sums
+  // are kept for them alone and the write-back runs on full waves.
+  for (uint32_t s0 = 0; s0 < B; s0 += kThreads) {
+    const uint32_t s = s0 + tid;
+    const bool hit = s < B && s_idx[s] != kNone;
+    const unsigned long long m = __ballot(hit);
+    uint32_t at = 0;
+    if (lane == 0 && m) at = atomicAdd(&s_nlist, (uint32_t)__popcll(m));
+    at = (uint32_t)__shfl((int)at, 0);
+    if (hit) {
+      at += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      s_idx[s] = (uint16_t)at;
+      if (at < N) s_list[at] = (uint16_t)s;
+    }
+  }
+  __syncthreads();
+  const uint32_t n_touched = s_nlist;
+  auto add_batch = [&](const uint32_t* at, const bool* ev, uint32_t c0) {
+    unsigned long long ek[kLaterBatch];
+    float4 v[kLaterBatch];
+    float qv[kLaterBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q) {
+      ek[q] = pv.stage_key[at[q]];
+      v[q] = pv.stage_v[at[q]];
+      qv[q] = kVar ? pv.stage_q[at[q]] : 0.0f;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kLaterBatch; ++q)
+      if (ev[q] && !(ek[q] & kLookupOnlyBit)) add(find(ek[q]), v[q], qv[q], c0);
   };
   auto answer_batch = [&](const uint32_t* at, const bool* ev, bool in_lds) {
     unsigned long long ek[kLaterBatch];
@@ -881,19 +983,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
                                             [&](const uint32_t* at, const bool* ev) { answer_batch(at, ev, false); });
   }
 
-  if (kFused && sat) atomicAdd(&s_sat, 1u);
-  __syncthreads();
-  if (tid == 0) {
-    if (s_dropped) atomicAdd(&tv.stats->dropped, (unsigned long long)s_dropped);
-    if (kFused) {
-      if (s_sat) atomicAdd(&tv.stats->saturated, (unsigned long long)s_sat);
-      BlockTouch* bt = &tv.touch[blk];
-      bt->last = n_touched;
-      bt->total += n_touched;
-    }
-  }
-  if (stats && tid < 16 && s_hist[tid])
-    atomicAdd(&tv.stats->probe_hist[tid], (unsigned long long)s_hist[tid]);
+  finish(n_touched);
 }
 
 // Threads of a merge block (768 for 4096 slots): the LDS of merge_lds_bytes
@@ -910,10 +1000,16 @@ static uint32_t merge_threads(uint32_t part_log2, uint32_t P) {
   return t;
 }
 
-template <bool kFused, int kThreads, bool kVar>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kVar ? 5 : 6)))
+// Threads of a dense launch's block: 1024 where its LDS leaves no room for a
+// second block on a CU (160 KB), else 512: 16 wavefronts a CU either way.
+static uint32_t merge_threads_dense(size_t lds) { return lds > 80 * 1024 ? 1024u : 512u; }
+
+constexpr int merge_waves(bool var, bool dense) { return dense ? 4 : var ? 5 : 6; }
+
+template <bool kFused, int kThreads, bool kVar, bool kDense>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(merge_waves(kVar, kDense))))
 k_merge(TableView tv, PartView pv, uint32_t ntiles, BlendParams bp, int32_t results) {
-  merge_body<kFused, kThreads, kVar>(tv, pv, ntiles, bp, blockIdx.x, results != 0);
+  merge_body<kFused, kThreads, kVar, kDense>(tv, pv, ntiles, bp, blockIdx.x, results != 0);
 }
 
 // ------------------------------------------------------------------ unstage
@@ -1013,8 +1109,29 @@ static size_t bin_lds(uint32_t P, uint32_t tile) {
   return hist > stage ? hist : stage;
 }
 
-static size_t merge_lds(const TableView& tv) {
-  return merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv));
+static size_t merge_lds(const TableView& tv, const PartView& pv) {
+  return merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv), pv.dense != 0);
+}
+
+// Where a frame of n records is dense: beyond 5/4 records a slot.  At the usual
+// eight records a touched cell a partition needs its second round from 5/2
+// records a slot on (2 with the further sum), but crowded partitions need it
+// sooner, and a wave's entries past its first batch are read three times
+// before that.  us a frame in rounds, and in one sweep: 2^22 slots in
+// partitions of 2^12, n / slots = 1: 154 and 173; 1.5: 253 and 257; 2: 388 and
+// 353; 3: 701 and 567.  2^20 in partitions of 2^11: 51.4 and 51.6; 70.4 and
+// 70.4; 109 and 87; 220 and 157; with the variance, 2^10: 64.7 and 61.7; 109
+// and 87; 169 and 105; 297 and 153.  16 records a slot in few cells (1,048,576
+// weighted records, 2^16 slots): 344 and 256.
+bool dense_records(uint64_t n, uint64_t slots) { return n > slots + slots / 4; }
+
+// (2^12 slots with the further sum take 184 KB, more than a CU has: such a
+// table's launches are never that dense, by its default width.)
+constexpr size_t kMostLds = 156 * 1024;
+
+bool dense_launch(uint64_t n, const TableView& tv) {
+  return dense_records(n, 1ull << tv.log2_slots) &&
+         merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv), true) <= kMostLds;
 }
 
 static bool tile_ok(uint32_t tile) {
@@ -1080,24 +1197,29 @@ hipError_t launch_bin(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const
   }
 }
 
-template <bool kFused, int kThreads, bool kVar>
+template <bool kFused, int kThreads, bool kVar, bool kDense>
 static hipError_t launch_merge_t(const TableView& tv, const PartView& pv, uint32_t ntiles, const BlendParams& bp,
                                  int32_t results, hipStream_t s) {
   static LdsLimit lim;  // one per instantiation
-  const size_t shm = merge_lds(tv);
-  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge<kFused, kThreads, kVar>), shm, &lim);
+  const size_t shm = merge_lds(tv, pv);
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge<kFused, kThreads, kVar, kDense>), shm, &lim);
   if (e != hipSuccess) return e;
-  k_merge<kFused, kThreads, kVar><<<1u << (tv.log2_slots - tv.part_log2), kThreads, shm, s>>>(tv, pv, ntiles, bp, results);
+  k_merge<kFused, kThreads, kVar, kDense><<<1u << (tv.log2_slots - tv.part_log2), kThreads, shm, s>>>(tv, pv, ntiles, bp, results);
   return hipGetLastError();
 }
 
 template <bool kFused, bool kVar>
 static hipError_t launch_merge_f(const TableView& tv, const PartView& pv, uint32_t ntiles, const BlendParams& bp,
                                  int32_t results, hipStream_t s) {
+  if (pv.dense) {
+    return merge_threads_dense(merge_lds(tv, pv)) == 1024
+               ? launch_merge_t<kFused, 1024, kVar, true>(tv, pv, ntiles, bp, results, s)
+               : launch_merge_t<kFused, 512, kVar, true>(tv, pv, ntiles, bp, results, s);
+  }
   switch (merge_threads(tv.part_log2, 1u << (tv.log2_slots - tv.part_log2))) {
-    case 768: return launch_merge_t<kFused, 768, kVar>(tv, pv, ntiles, bp, results, s);
-    case 384: return launch_merge_t<kFused, 384, kVar>(tv, pv, ntiles, bp, results, s);
-    default: return launch_merge_t<kFused, 192, kVar>(tv, pv, ntiles, bp, results, s);
+    case 768: return launch_merge_t<kFused, 768, kVar, false>(tv, pv, ntiles, bp, results, s);
+    case 384: return launch_merge_t<kFused, 384, kVar, false>(tv, pv, ntiles, bp, results, s);
+    default: return launch_merge_t<kFused, 192, kVar, false>(tv, pv, ntiles, bp, results, s);
   }
 }
 
@@ -1213,22 +1335,24 @@ k_bin_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
 }
 
 // As many threads per block as the widest session's partitions take; kVar: a
-// session keeps the luminance variance.
-template <int kThreads, bool kVar>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kVar ? 5 : 6))) k_merge_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
+// session keeps the luminance variance; kDense: the sessions of many records
+// a slot, which a launch of their own takes (the others' blocks end at once).
+template <int kThreads, bool kVar, bool kDense>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(merge_waves(kVar, kDense))))
+k_merge_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {
   const BatchSession& S = ss[find_session(bg, k, blockIdx.x)];
   const uint32_t local = blockIdx.x - S.part_begin;
-  if (local >= S.nparts) return;
+  if (local >= S.nparts || (S.pv.dense != 0) != kDense) return;
   const TableView tv = S.tv;
   const PartView pv = S.pv;
   const BlendParams bp = S.bp;
   if constexpr (kVar) {
     if (tv.var) {
-      merge_body<true, kThreads, true>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
+      merge_body<true, kThreads, true, kDense>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
       return;
     }
   }
-  merge_body<true, kThreads, false>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
+  merge_body<true, kThreads, false, kDense>(tv, pv, S.ntiles, bp, local, S.fused_query != 0);
 }
 
 // A session whose queries are its records takes one unstage block per tile;
@@ -1285,21 +1409,21 @@ static hipError_t launch_bin_batch_x(uint32_t x, const BatchSession* d_ss, const
   }
 }
 
-template <int kThreads, bool kVar>
+template <int kThreads, bool kVar, bool kDense>
 static hipError_t launch_merge_batch_v(const BatchSession* d_ss, const uint32_t* bg, uint32_t k, uint32_t parts,
                                        size_t lds, hipStream_t s) {
   static LdsLimit lim;  // one per instantiation
-  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge_batch<kThreads, kVar>), lds, &lim);
+  hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_merge_batch<kThreads, kVar, kDense>), lds, &lim);
   if (e != hipSuccess) return e;
-  k_merge_batch<kThreads, kVar><<<parts, kThreads, lds, s>>>(d_ss, bg, k);
+  k_merge_batch<kThreads, kVar, kDense><<<parts, kThreads, lds, s>>>(d_ss, bg, k);
   return hipGetLastError();
 }
 
-template <int kThreads>
+template <int kThreads, bool kDense>
 static hipError_t launch_merge_batch_t(bool var, const BatchSession* d_ss, const uint32_t* bg, uint32_t k,
                                        uint32_t parts, size_t lds, hipStream_t s) {
-  return var ? launch_merge_batch_v<kThreads, true>(d_ss, bg, k, parts, lds, s)
-             : launch_merge_batch_v<kThreads, false>(d_ss, bg, k, parts, lds, s);
+  return var ? launch_merge_batch_v<kThreads, true, kDense>(d_ss, bg, k, parts, lds, s)
+             : launch_merge_batch_v<kThreads, false, kDense>(d_ss, bg, k, parts, lds, s);
 }
 
 hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, const uint32_t* h_begins,
@@ -1307,9 +1431,13 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   if (k == 0) return hipSuccess;
   if (k > stride) return hipErrorInvalidValue;
   uint32_t tiles = 0, parts = 0, qblks = 0, trans = 0;
-  size_t lds_b = 0, lds_m = 0, lds_q = 0;
-  uint32_t x = 0, part_log2 = 0;  // what any session's records carry; the widest partitions
-  bool var = false;
+  size_t lds_b = 0, lds_q = 0;
+  uint32_t x = 0;  // what any session's records carry
+  struct {
+    bool any, var;
+    uint32_t part_log2;  // the widest partitions
+    size_t lds;
+  } merge[2] = {};  // of the ordinary and of the dense sessions
   for (uint32_t i = 0; i < k; ++i) {
     const BatchSession& S = h_ss[i];
     if (h_begins[i] != S.tile_begin || h_begins[stride + i] != S.part_begin ||
@@ -1321,11 +1449,13 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
         S.ntrans != (S.pv.runs_t ? transpose_blocks(S.ntiles, 1u << (S.tv.log2_slots - S.tv.part_log2)) : 0u))
       return hipErrorInvalidValue;
     const uint32_t P = 1u << (S.tv.log2_slots - S.tv.part_log2);
-    const size_t lb = bin_lds(P, S.pv.tile), lm = merge_lds(S.tv);
+    const size_t lb = bin_lds(P, S.pv.tile), lm = merge_lds(S.tv, S.pv);
     lds_b = lb > lds_b ? lb : lds_b;
-    lds_m = lm > lds_m ? lm : lds_m;
-    part_log2 = S.tv.part_log2 > part_log2 ? S.tv.part_log2 : part_log2;
-    var = var || S.tv.var;
+    auto& mg = merge[S.pv.dense ? 1 : 0];
+    mg.any = true;
+    mg.lds = lm > mg.lds ? lm : mg.lds;
+    mg.part_log2 = S.tv.part_log2 > mg.part_log2 ? S.tv.part_log2 : mg.part_log2;
+    mg.var = mg.var || S.tv.var;
     if ((S.fused_query != 0) != (S.pv.perm != nullptr)) return hipErrorInvalidValue;
     if (S.fused_query) {
       if (S.nq != S.n || S.nqblk != S.ntiles) return hipErrorInvalidValue;
@@ -1358,12 +1488,22 @@ hipError_t launch_batch(const BatchSession* d_ss, const uint32_t* d_begins, cons
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (trans) k_transpose_batch<<<trans, kTransposeThreads, 0, s>>>(d_ss, bg_trans, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  switch (merge_threads(part_log2)) {
-    case 768: e = launch_merge_batch_t<768>(var, d_ss, bg_part, k, parts, lds_m, s); break;
-    case 384: e = launch_merge_batch_t<384>(var, d_ss, bg_part, k, parts, lds_m, s); break;
-    default: e = launch_merge_batch_t<192>(var, d_ss, bg_part, k, parts, lds_m, s); break;
+  if (merge[0].any) {
+    const auto& mg = merge[0];
+    switch (merge_threads(mg.part_log2)) {
+      case 768: e = launch_merge_batch_t<768, false>(mg.var, d_ss, bg_part, k, parts, mg.lds, s); break;
+      case 384: e = launch_merge_batch_t<384, false>(mg.var, d_ss, bg_part, k, parts, mg.lds, s); break;
+      default: e = launch_merge_batch_t<192, false>(mg.var, d_ss, bg_part, k, parts, mg.lds, s); break;
+    }
+    if (e != hipSuccess) return e;
   }
-  if (e != hipSuccess) return e;
+  if (merge[1].any) {
+    const auto& mg = merge[1];
+    e = merge_threads_dense(mg.lds) == 1024
+            ? launch_merge_batch_t<1024, true>(mg.var, d_ss, bg_part, k, parts, mg.lds, s)
+            : launch_merge_batch_t<512, true>(mg.var, d_ss, bg_part, k, parts, mg.lds, s);
+    if (e != hipSuccess) return e;
+  }
   if (qblks) k_query_batch<<<qblks, kQueryBlock, lds_q, s>>>(d_ss, bg_qblk, k);
   return hipGetLastError();
 }

@@ -1,0 +1,111 @@
+"""Launches of more than 5/4 records a slot, which the merge sums slot by slot
+in one sweep: at and past the change, with one batch of entries a wavefront
+and with several, every kind of table and every state format, fused and as
+separate calls, alone and batched beside ordinary sessions, against the
+oracle."""
+import numpy as np
+import pytest
+
+from tests.helpers import records, to_device
+
+pytestmark = pytest.mark.gpu
+RTOL = 1e-5
+CFG = dict(log2_slots=13, e_min=-2, kappa=0.0, normal_bins_log2=0)  # 4096 cells in 8192 slots
+
+
+def _records(n, seed, weighted=False):
+    rng = np.random.default_rng(seed)
+    p = rng.uniform(-2.0, 2.0, (3, n))
+    run = np.arange(n) // 3 * 3
+    nrm = rng.normal(size=(3, n))
+    v = rng.exponential(size=(3, n))
+    v[1, rng.random(n) < 0.01] = np.nan  # rejected as samples, answered as queries
+    nrm[0, rng.random(n) < 0.01] = np.inf  # no key
+    extra = {"weight": np.where(rng.random(n) < 0.1, 0.0, rng.uniform(0.25, 2.0, n))} if weighted else {}
+    return records(n, px=p[0, run], py=p[1, run], pz=p[2, run], nx=nrm[0], ny=nrm[1], nz=nrm[2],
+                   r=v[0], g=v[1], b=v[2], **extra)
+
+
+def _close(out, found, orc, rec):
+    want, hit = orc.query(rec)
+    assert np.array_equal(found.cpu().numpy(), hit)
+    err = np.abs(out.cpu().numpy() - want) / np.maximum(np.abs(want), 1e-30)
+    assert float(err[:, hit.astype(bool)].max(initial=0.0)) <= RTOL
+
+
+def _cells(t, orc, kind):
+    st, ex, o = t.stats(), t.export(), orc.export()
+    assert st["dropped"] == 0 and st["skipped"] == orc.counters()["skipped"]
+    assert np.array_equal(ex["keys"], o["keys"])
+    assert np.allclose(ex["c_old"].astype(np.float64), o["c_old"], rtol=1e-6 if kind == "weighted" else 0)
+    if kind == "variance":
+        keys, var = t.export_variance()
+        o_keys, o_var = orc.export_variance()
+        m = o["L"][0] * 0.25 + o["L"][1] * 0.5 + o["L"][2] * 0.25
+        assert np.array_equal(keys, o_keys)
+        assert np.all(np.abs(var - o_var) <= RTOL * (o_var + m * m) + 1e-30)
+
+
+def _table(psf, kind, part_log2, **kw):
+    return psf.Table(**CFG, max_probe=1 << (part_log2 or 8), part_log2=part_log2, weighted=int(kind == "weighted"),
+                     flags=psf.PSF_FLAG_TRACK_VARIANCE if kind == "variance" else 0, **kw)
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("n", [10240, 10241, 90011])
+@pytest.mark.parametrize("kind,part_log2", [("plain", 12), ("plain", 11), ("plain", 8), ("weighted", 11),
+                                            ("weighted", 10), ("variance", 11), ("variance", 8)])
+def test_dense_launches_match_the_oracle(kind, part_log2, n, fused):
+    import oracle
+    from paper_2005_07547_amd import psf
+    t = _table(psf, kind, part_log2)
+    orc = oracle.Oracle(**CFG, weighted=int(kind == "weighted"))
+    for it in range(2):
+        rec = _records(n, 10 * it + part_log2, kind == "weighted")
+        d = to_device(rec)
+        if fused:
+            out, found = t.iterate(d)
+        else:
+            t.insert(d)
+            t.update()
+            out, found = t.query(d)
+        orc.insert(rec)
+        orc.update()
+        _close(out, found, orc, rec)
+    _cells(t, orc, kind)
+
+
+@pytest.mark.parametrize("dtype", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("part_log2", [8, 12])
+def test_dense_answers_equal_a_lookup_in_every_state_format(dtype, part_log2):
+    """Bit for bit, with keys that find no slot in 4 probes."""
+    from paper_2005_07547_amd import psf
+    t = psf.Table(**CFG, part_log2=part_log2, max_probe=4, state_dtype=dtype)
+    for it in range(3):
+        d = to_device(_records(30011, it))
+        out, found = t.iterate(d)
+        again, hit = t.query(d)
+        assert np.array_equal(found.cpu().numpy(), hit.cpu().numpy())
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), again.cpu().numpy().view(np.uint32))
+    assert t.stats()["dropped"] > 0
+
+
+def test_dense_and_ordinary_sessions_share_a_batch():
+    import oracle
+    from paper_2005_07547_amd import psf
+    kinds = [("plain", 12, 4000), ("variance", 11, 40003), ("plain", 8, 10241), ("weighted", 10, 9000),
+             ("weighted", 11, 12289), ("variance", 10, 500), ("plain", 12, 30000)]
+    for some in (kinds, kinds[1:3] + kinds[4:5], kinds[6:]):  # both sorts, and dense ones alone
+        tabs = [_table(psf, k, p, max_batch=50000) for k, p, _ in some]
+        orcs = [oracle.Oracle(**CFG, weighted=int(k == "weighted")) for k, _, _ in some]
+        batch = psf.Batch(len(some))
+        for it in range(2):
+            recs = [_records(n, 100 * it + i, k == "weighted") for i, (k, _, n) in enumerate(some)]
+            answers = batch.iterate(tabs, [to_device(r) for r in recs])
+            for (o, f), orc, rec in zip(answers, orcs, recs):
+                orc.insert(rec)
+                orc.update()
+                _close(o, f, orc, rec)
+        for t, orc, (k, _, _) in zip(tabs, orcs, some):
+            _cells(t, orc, k)
+        batch.close()

@@ -1,0 +1,33 @@
+"""Device memory of a table by its configuration (no GPU): the default
+partition width where launches can be dense."""
+import ctypes
+
+import pytest
+
+
+def _bytes(**kw):
+    from paper_2005_07547_amd import psf
+    return psf.load().psf_table_bytes(ctypes.byref(psf.make_config(**kw)))
+
+
+@pytest.mark.parametrize("kind", ["plain", "weighted", "variance"])
+@pytest.mark.parametrize("log2_slots", [18, 20, 21, 23])
+def test_default_width_leaves_room_for_dense_launches(kind, log2_slots):
+    """A weighted or variance table whose launches can hold more than 5/4
+    records a slot takes partitions whose every slot's sums fit a block: 2^10
+    slots below 2^21, 2^11 from there on; others 2^11, and 2^12 from 2^21."""
+    from paper_2005_07547_amd import psf
+    cfg = dict(log2_slots=log2_slots, bin_per=8, weighted=int(kind == "weighted"),
+               flags=psf.PSF_FLAG_TRACK_VARIANCE if kind == "variance" else 0)
+    most = (1 << log2_slots) * 5 // 4  # a multiple of the tile
+    for max_batch, crowded in ((most, False), (most + 1, True)):
+        got = _bytes(**cfg, max_batch=max_batch)
+        # the offset tables tell the width: (partitions + 1) * tiles words, twice (rows of 4 words in the second)
+        tiles = (max_batch + 4095) // 4096
+        width = {w: _bytes(**cfg, max_batch=max_batch, part_log2=w) for w in (10, 11)}
+        step = (width[10] - width[11]) / (1 << (log2_slots - 11))  # bytes a partition
+        parts = (1 << (log2_slots - 10)) - (width[10] - got) / step
+        want = log2_slots - (12 if log2_slots >= 21 else 11)
+        if crowded and kind != "plain":
+            want = log2_slots - (11 if log2_slots >= 21 else 10)
+        assert round(parts) == 1 << want, (parts, want, tiles)
