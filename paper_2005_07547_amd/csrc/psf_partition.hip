@@ -705,7 +705,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
     }
     return o;
   };
-  bool sat = false;
+  uint32_t n_sat = 0;  // cells of this thread whose 16-bit store was clamped
   // Writes touched cell c of the round back (slot s of the partition).
   auto write_back = [&](uint32_t c, uint32_t s, const Old& old) {
     const uint64_t g = base + s;
@@ -730,7 +730,9 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
         tv.var[g] = blend_variance(old.v, alpha, luma32(L[0], L[1], L[2]), m, s2);
       }
       uint32_t enc[4], pad;
+      bool sat = false;
       encode_state(bp.dtype, out[0], out[1], out[2], enc, pad, sat);
+      n_sat += sat ? 1u : 0u;
       Slot nw;
       nw.key = k;
       nw.c_old = counter_add(old.slot.c_old, cn, wtd);
@@ -799,7 +801,7 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
   };
   // Counters of the partition, once every thread is done with it.
   auto finish = [&](uint32_t n_touched) {
-    if (kFused && sat) atomicAdd(&s_sat, 1u);
+    if (kFused && n_sat) atomicAdd(&s_sat, n_sat);
     __syncthreads();
     if (tid == 0) {
       if (s_dropped) atomicAdd(&tv.stats->dropped, (unsigned long long)s_dropped);
