@@ -239,8 +239,7 @@ Layout layout_of(const psf_config& c) {
   if (L.part) {
     L.tiles = (uint32_t)(L.cap / tile);
     // rows of the offset tables: also the smaller tiles of a small launch
-    const uint64_t small = (L.cap + 1023) / 1024;
-    if (!c.bin_per) L.tiles = (uint32_t)std::max<uint64_t>(L.tiles, std::min<uint64_t>(small, psf::kSmallTiles));
+    if (!c.bin_per) L.tiles = std::max(L.tiles, psf::small_tiles(L.cap, (uint32_t)P));
     L.stage_key = off;
     off = align_up(off + L.cap * 8, 256);
     L.stage_v = off;

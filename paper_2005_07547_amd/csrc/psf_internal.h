@@ -150,6 +150,9 @@ bool bin_per_ok(uint32_t per);          // supported records per thread of the b
 uint32_t bin_tile(uint32_t per);        // records per binning tile
 constexpr uint32_t kSmallTiles = 512;    // most tiles of a launch that takes smaller ones
 uint32_t launch_tile(uint64_t n, uint32_t nparts);  // records per tile at the default width
+// Most tiles smaller than the default's that a launch of up to cap records
+// takes (0 where the partitions are too many for them).
+uint32_t small_tiles(uint64_t cap, uint32_t nparts);
 // Whether a launch of n records sums every slot of a partition in one sweep,
 // or (the default) the touched ones in rounds; and whether its records are
 // that many, whatever its partitions.

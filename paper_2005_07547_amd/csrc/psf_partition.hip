@@ -62,6 +62,16 @@ uint32_t launch_tile(uint64_t n, uint32_t nparts) {
   return 4096;
 }
 
+uint32_t small_tiles(uint64_t cap, uint32_t nparts) {
+  uint64_t most = 0;
+  for (uint32_t tile = 1024; tile < 4096; tile *= 2) {
+    if (2 * nparts > tile) continue;
+    const uint64_t n = cap < (uint64_t)kSmallTiles * tile ? cap : (uint64_t)kSmallTiles * tile;
+    if ((n + tile - 1) / tile > most) most = (n + tile - 1) / tile;
+  }
+  return (uint32_t)most;
+}
+
 // Exclusive prefix sum of cnt[0..m) in LDS, in place; returns the total.
 // Called by all kThreads threads of the block.
 template <int kThreads>

@@ -31,3 +31,26 @@ def test_default_width_leaves_room_for_dense_launches(kind, log2_slots):
         if crowded and kind != "plain":
             want = log2_slots - (11 if log2_slots >= 21 else 10)
         assert round(parts) == 1 << want, (parts, want, tiles)
+
+
+@pytest.mark.parametrize("log2_slots,part_log2,max_batch,rows", [
+    (24, 12, 1 << 19, 128),   # 4096 partitions: tiles of 4096 records only
+    (21, 11, 1 << 19, 256),   # 1024: of 2048 too
+    (20, 11, 1 << 19, 512),   # 512: of 1024 too
+    (20, 11, 1 << 18, 256),
+    (20, 11, 5000, 8),        # two tiles' capacity
+    (20, 11, 1 << 22, 1024),
+    (22, 10, 1 << 16, 16),
+])
+def test_offset_tables_hold_the_tiles_a_launch_can_take(log2_slots, part_log2, max_batch, rows):
+    """Rows for the binning tiles of 1024 and 2048 records only where the
+    partitions leave a launch the choice of them."""
+    S, P = 1 << log2_slots, 1 << (log2_slots - part_log2)
+    cap = -(-max_batch // 4096) * 4096
+    words = (P + 1) * rows + (P + 1) * (-(-rows // 4) * 4)
+    fixed = _bytes(log2_slots=log2_slots, part_log2=part_log2, max_batch=max_batch, bin_per=8)
+    tiles = cap // 4096
+    fixed_words = (P + 1) * tiles + (P + 1) * (-(-tiles // 4) * 4)
+    got = _bytes(log2_slots=log2_slots, part_log2=part_log2, max_batch=max_batch)
+    assert S * 56 < got
+    assert abs((got - fixed) - 4 * (words - fixed_words)) <= 1024  # (each array is rounded up to 256 bytes)
