@@ -494,30 +494,45 @@ __device__ __forceinline__ float ld_once_at(const float* p, uint32_t i) {
 __device__ __forceinline__ void st_once(float* p, float v) { __builtin_nontemporal_store(v, p); }
 
 // One vertex of a structure-of-arrays query set: element i of the arrays
-// from a wave-uniform start on.  Every load is unconditional (absent arrays
-// alias the positions) and all are waited for together: under the key's
-// conditions they would be one dependent round trip after another.
+// from a wave-uniform start on (arrays the caller left out read as 0).  The
+// loads that every vertex needs are all issued before the first wait: under
+// the key's conditions they would be one dependent round trip after another.
+// The roughness comes first, and the direction, 12 of 40 bytes, only where it
+// makes the vertex glossy, while the others are on their way (3,686,400
+// lookups at diffuse vertices 81.0 -> 73.6 us, with a quarter glossy 79.3 and
+// 80.1).
 struct Vertex {
   float p[3], n[3], o[3], rough, fp;
 };
+
+// The direction (x, y, z) of a vertex of roughness rough, in a table of
+// threshold thr (+inf: keyed on the direction everywhere); +z, whose bin costs
+// a wave nothing beyond the others', where it is not glossy.
+__device__ __forceinline__ void load_direction(const float* x, const float* y, const float* z, uint64_t start,
+                                               uint32_t i, float rough, float thr, float o[3]) {
+  o[0] = o[1] = 0.0f;
+  o[2] = 1.0f;
+  if (rough < thr) {
+    o[0] = ld_once_at(x + start, i);
+    o[1] = ld_once_at(y + start, i);
+    o[2] = ld_once_at(z + start, i);
+  }
+}
+
 template <class Q>
-__device__ __forceinline__ Vertex load_vertex(const Q& q, uint64_t start, uint32_t i) {
+__device__ __forceinline__ Vertex load_vertex(const Q& q, float thr, uint64_t start, uint32_t i) {
   const bool hr = q.rough != nullptr, hf = q.footprint != nullptr;
   Vertex v;
+  v.o[0] = v.o[1] = v.o[2] = v.rough = v.fp = 0.0f;
+  if (hr) v.rough = ld_once_at(q.rough + start, i);
   v.p[0] = ld_once_at(q.px + start, i);
   v.p[1] = ld_once_at(q.py + start, i);
   v.p[2] = ld_once_at(q.pz + start, i);
   v.n[0] = ld_once_at(q.nx + start, i);
   v.n[1] = ld_once_at(q.ny + start, i);
   v.n[2] = ld_once_at(q.nz + start, i);
-  v.o[0] = v.o[1] = v.o[2] = v.rough = v.fp = 0.0f;
-  if (hr) {
-    v.o[0] = ld_once_at(q.ox + start, i);
-    v.o[1] = ld_once_at(q.oy + start, i);
-    v.o[2] = ld_once_at(q.oz + start, i);
-    v.rough = ld_once_at(q.rough + start, i);
-  }
   if (hf) v.fp = ld_once_at(q.footprint + start, i);
+  if (hr) load_direction(q.ox, q.oy, q.oz, start, i, v.rough, thr, v.o);
   return v;
 }
 

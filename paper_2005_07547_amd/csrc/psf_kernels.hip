@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(256) k_query(QryPtrs q, uint64_t n, KeyParams 
                                                int32_t dtype, float* out, uint8_t* found) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
   loaded(v);
   float rgb[3];
   const uint8_t hit = lookup_key(tv, dtype, vertex_key(kp, q, v), rgb);
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(256) k_query_hier(QryPtrs q, uint64_t n, uint3
                                                     uint8_t* level_out) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
   loaded(v);
   // the bins once, the position at each level
   int ok = (int)finite3(v.p[0], v.p[1], v.p[2]) & (int)finite3(v.n[0], v.n[1], v.n[2]);
@@ -325,13 +325,9 @@ __global__ void __launch_bounds__(kEstThreads) k_estimate(EstPtrs a, uint64_t n,
   const uint32_t last = n - start < kEstThreads ? (uint32_t)(n - start) - 1 : kEstThreads - 1;
   const uint32_t t = threadIdx.x < last ? threadIdx.x : last;
   const bool hr = a.qo.rough != nullptr, hf = a.qo.footprint != nullptr;
-  const Vertex v = load_vertex(a.qo, start, t);
+  const Vertex v = load_vertex(a.qo, kp_o.rough_thr, start, t);
   float wi[3] = {0.0f, 0.0f, 0.0f};
-  if (hr) {
-    wi[0] = ld_once_at(a.qi.ox + start, t);
-    wi[1] = ld_once_at(a.qi.oy + start, t);
-    wi[2] = ld_once_at(a.qi.oz + start, t);
-  }
+  if (hr) load_direction(a.qi.ox, a.qi.oy, a.qi.oz, start, t, v.rough, kp_i.rough_thr, wi);
   const float g[3] = {ld_once_at(a.gr + start, t), ld_once_at(a.gg + start, t), ld_once_at(a.gb + start, t)};
   const float w = ld_once_at(a.wp + start, t);
   loaded(v);
@@ -389,7 +385,7 @@ __global__ void __launch_bounds__(256) k_step_samples(StepPtrs a, uint64_t n, Ke
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
   const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
-  const Vertex v = load_vertex(a.next, start, ti);
+  const Vertex v = load_vertex(a.next, kp.rough_thr, start, ti);
   const bool le = a.le_r != nullptr;
   float e[3] = {0.0f, 0.0f, 0.0f};
   if (le) {
@@ -817,7 +813,7 @@ __global__ void __launch_bounds__(256) k_query_sh(QryPtrs q, uint64_t n, KeyPara
                                                   uint8_t* found) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
   loaded(v);
   const uint64_t key = vertex_key(kp, q, v);
   float rgb[3] = {0.0f, 0.0f, 0.0f};

@@ -1388,7 +1388,7 @@ __global__ void __launch_bounds__(kQueryBlock) k_query_batch(const BatchSession*
   const TableView tv = S.tv;
   const KeyParams kp = S.kp;
   const QryPtrs q = S.q;
-  const Vertex v = load_vertex(q, start, threadIdx.x < last ? threadIdx.x : last);
+  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
   loaded(v);
   float rgb[3];
   const uint8_t hit = lookup_key(tv, S.bp.dtype, vertex_key(kp, q, v), rgb);
