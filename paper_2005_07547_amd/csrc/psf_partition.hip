@@ -1141,9 +1141,12 @@ bool dense_records(uint64_t n, uint64_t slots) { return n > slots + slots / 4; }
 // table's launches are never that dense, by its default width.)
 constexpr size_t kMostLds = 156 * 1024;
 
+bool dense_fits(const TableView& tv) {
+  return merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv), true) <= kMostLds;
+}
+
 bool dense_launch(uint64_t n, const TableView& tv) {
-  return dense_records(n, 1ull << tv.log2_slots) &&
-         merge_lds_bytes(1u << tv.part_log2, tv.var || weighted(tv), true) <= kMostLds;
+  return dense_records(n, 1ull << tv.log2_slots) && dense_fits(tv);
 }
 
 static bool tile_ok(uint32_t tile) {
