@@ -25,15 +25,18 @@ __device__ __forceinline__ uint64_t find_or_claim(const TableView& tv, uint64_t 
   for (uint32_t i = 0; i < tv.max_probe; ++i) {
     const uint64_t s = ps.at(i);
     // A slot's key is set once, and its mirror after it: a key read from the
-    // mirror by an ordinary load is the slot's, and only one still empty
-    // there is looked at (and claimed) in the slot.
-    unsigned long long cur = tv.keys[s];
+    // mirror is the slot's, and only one still empty there is looked at (and
+    // claimed) in the slot.  Other blocks write the mirror meanwhile, so both
+    // sides are atomic; the load's scope leaves it to the caches, since a key
+    // that it misses is found in the slot.
+    unsigned long long cur = __hip_atomic_load(&tv.keys[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     if (cur == kEmpty) {
       unsigned long long* kp = &tv.slots[s].key;
       cur = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (cur == kEmpty) {
         cur = atomicCAS(kp, kEmpty, (unsigned long long)key);
-        if (cur == kEmpty) tv.keys[s] = key;  // this lane claimed the slot
+        if (cur == kEmpty)  // this lane claimed the slot
+          __hip_atomic_store(&tv.keys[s], (unsigned long long)key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
       }
     }
     if (cur == kEmpty || cur == key) {
