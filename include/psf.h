@@ -441,7 +441,7 @@ psf_status psf_export_sh_cells(psf_table* t, uint64_t* keys, uint32_t* c_old, fl
                                uint64_t* count, psf_stream stream);
 
 /* Batched form: one iteration (insert, temporal update, query) of k
- * independent sessions, each with its own table, in three launches that
+ * independent sessions, each with its own table, in a few launches that
  * cover every session (binning, merge + blend, lookup).  Each session's
  * result equals the same session run alone through psf_iterate.  Sessions
  * that cannot join the batch (direct insert strategy, samples pending from

@@ -407,7 +407,7 @@ PSF_API psf_status psf_create_table(const psf_config* cfg, void* device_buffer, 
   if (!validate(cfg, &why)) return fail(PSF_INVALID_ARGUMENT, why);
   if (cfg->payload == PSF_PAYLOAD_SH2_YCOCG &&
       (cfg->state_dtype != PSF_STATE_F32 || cfg->insert_mode == PSF_INSERT_PARTITIONED))
-    return fail(PSF_NOT_SUPPORTED, "the SH payload takes F32 state and the direct insert strategy");
+    return fail(PSF_NOT_SUPPORTED, "the SH payload takes F32 state and insert_mode AUTO or DIRECT");
   if ((cfg->flags & PSF_FLAG_TRACK_VARIANCE) && (cfg->payload != PSF_PAYLOAD_RGB || cfg->weighted))
     return fail(PSF_NOT_SUPPORTED, "the luminance variance is kept for unweighted RGB tables only");
   const Layout L = layout_of(*cfg);

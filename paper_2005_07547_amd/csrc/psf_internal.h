@@ -202,8 +202,9 @@ hipError_t launch_sample_paths(const PathPrim* prims, uint32_t np, const PathCam
                                uint64_t n_paths, const PathOut& out, hipStream_t s);
 hipError_t launch_philox(const uint32_t* ctr, const uint32_t* key, uint64_t n, uint32_t* out, hipStream_t s);
 
-// SH payload tables (Sec. 2.6): direct insert into binary64 frame sums,
-// streaming fit + blend, lookup evaluating the luminance at the normal.
+// SH payload tables (Sec. 2.6): direct insert into binary64 frame sums (or the
+// partitioned one below), streaming fit + blend, lookup evaluating the luminance
+// at the normal.
 hipError_t launch_insert_sh(const RecPtrs& rec, uint64_t n, const KeyParams& kp, const TableView& tv,
                             hipStream_t s);
 // Partitioned insert of an SH payload table's binned records (launch_bin

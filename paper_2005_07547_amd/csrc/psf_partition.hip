@@ -20,8 +20,9 @@
 //            finds or claims each one's slot, lists the touched slots, and
 //            accumulates count (u32) and sums (binary64; also the weights
 //            of a weighted table and the squared luminances of one that
-//            keeps the variance) of the touched cells with LDS atomics,
-//            then writes them back:
+//            keeps the variance) of the touched cells with LDS atomics
+//            (a dense launch: of every slot, as the entries are read), then
+//            writes them back:
 //            either adding into the global accumulators (plain insert) or,
 //            when the whole frame is in this launch, applying the temporal
 //            blend (Eq. 10-11) directly so the accumulators never touch HBM;
@@ -163,13 +164,13 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
 
 // Threads and records per thread of the binning pass: a tile of 4096 records
 // takes 1024 threads with 4 records each (6144: 768 with 8, or 512 with 12
-// where records carry more; 8192: 1024 with 8).  The pass waits on one dependent step after
-// another (record loads, LDS ranks, scan, staging), so twice the wavefronts
-// with half the records each hide more of it: 70.6 -> 62.0 us for 3,686,400
-// records (900 tiles) against 512 threads with 8, 174 -> 163 us for 1688
-// tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
-// (one of 8192 records, by its LDS; twelve weighted records a thread spill
-// at 128 registers).
+// where records carry more; 8192: 1024 with 8).  The pass waits on one dependent
+// step after another (record loads, LDS ranks, scan, staging), so twice the
+// wavefronts with half the records each hide more of it: 70.6 -> 62.0 us for
+// 3,686,400 records (900 tiles) against 512 threads with 8, 174 -> 163 us for
+// 1688 tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
+// (one of 8192 records, by its LDS; twelve weighted records a thread spill at
+// 128 registers and run one block a CU at 137).
 constexpr int bin_waves(uint32_t threads, uint32_t per, bool weights) {
   return threads * per > 6144 ? 4 : per > 8 && weights ? 3 : (int)threads / 128;
 }
@@ -187,8 +188,8 @@ __device__ __forceinline__ void bin_body(const RecPtrs& rec, uint64_t n, const K
   const uint64_t t0 = (uint64_t)tile * (kThreads * kPer);
   // records merge into runs only with integer counters and no weights; a
   // table that keeps the variance also sums each run's squared luminances
-  // (in registers: with 8 records per thread; with more, its records stay
-  // entries of their own)
+  // (in registers, in tiles of up to 4096 records; in larger ones its records
+  // stay entries of their own)
   const bool var = tv.var != nullptr;
   constexpr bool kQRuns = kThreads * kPer <= 4096;
   const bool premerge = !kW && !kN && (kQRuns || !var);
@@ -1000,7 +1001,8 @@ __device__ __forceinline__ void merge_body(const TableView& tv, const PartView& 
 
 // Threads of a merge block (768 for 4096 slots): the LDS of merge_lds_bytes
 // leaves room for 24 such wavefronts on a CU, at 80 registers (a table that
-// keeps the variance holds one more value an entry: 20 at 96).
+// keeps the variance holds one more value an entry, and 96 registers leave 20:
+// one block of 768 threads, three of 384).
 static uint32_t merge_threads(uint32_t part_log2) { return part_log2 >= 12 ? 768u : part_log2 == 11 ? 384u : 192u; }
 
 // The same for a launch of P partitions that does not fill 256 CUs: twice or
@@ -1332,8 +1334,6 @@ __device__ __forceinline__ void bin_session(const BatchSession& S, uint32_t loca
     bin_body<kThreads, kPer, kW>(rec, n, kp, tv, pv, local);
 }
 
-// (the batch instantiations that carry several bodies would spill heavily
-// under the same cap)
 template <uint32_t kThreads, uint32_t kPer, uint32_t kX>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bin_waves(kThreads, kPer, kX & kXWeight))))
 k_bin_batch(const BatchSession* ss, const uint32_t* bg, uint32_t k) {

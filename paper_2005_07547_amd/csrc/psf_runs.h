@@ -64,7 +64,7 @@ struct RunReader {
   }
 
   __device__ __forceinline__ RunChunk chunk_of(uint32_t c0) const {
-    const uint32_t t = c0 + lane * kRunsPerLane;  // a multiple of 4
+    const uint32_t t = c0 + lane * kRunsPerLane;  // (a multiple of 4 in a transposed table)
     uint32_t r_lo[kRunsPerLane], r_hi[kRunsPerLane];
     if (pv.runs_t) {
       // transposed table: two 16-byte loads (t + 3 < stride: inside the row)
