@@ -512,15 +512,17 @@ __device__ __forceinline__ void load_direction(const float* x, const float* y, c
                                                uint32_t i, float rough, float thr, float o[3]) {
   o[0] = o[1] = 0.0f;
   o[2] = 1.0f;
-  if (rough < thr) {
+  if (thr > 3.402823466e38f || rough < thr) {  // (the first test is wave-uniform)
     o[0] = ld_once_at(x + start, i);
     o[1] = ld_once_at(y + start, i);
     o[2] = ld_once_at(z + start, i);
   }
 }
 
+// All but the direction, which load_vertex_direction adds once everything
+// else that the caller loads is on its way.
 template <class Q>
-__device__ __forceinline__ Vertex load_vertex(const Q& q, float thr, uint64_t start, uint32_t i) {
+__device__ __forceinline__ Vertex load_vertex(const Q& q, uint64_t start, uint32_t i) {
   const bool hr = q.rough != nullptr, hf = q.footprint != nullptr;
   Vertex v;
   v.o[0] = v.o[1] = v.o[2] = v.rough = v.fp = 0.0f;
@@ -532,8 +534,11 @@ __device__ __forceinline__ Vertex load_vertex(const Q& q, float thr, uint64_t st
   v.n[1] = ld_once_at(q.ny + start, i);
   v.n[2] = ld_once_at(q.nz + start, i);
   if (hf) v.fp = ld_once_at(q.footprint + start, i);
-  if (hr) load_direction(q.ox, q.oy, q.oz, start, i, v.rough, thr, v.o);
   return v;
+}
+template <class Q>
+__device__ __forceinline__ void load_vertex_direction(const Q& q, float thr, uint64_t start, uint32_t i, Vertex& v) {
+  if (q.rough) load_direction(q.ox, q.oy, q.oz, start, i, v.rough, thr, v.o);
 }
 
 // (an empty statement that uses the values, so their loads issue before it)

@@ -267,7 +267,9 @@ __global__ void __launch_bounds__(256) k_query(QryPtrs q, uint64_t n, KeyParams 
                                                int32_t dtype, float* out, uint8_t* found) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
+  const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
+  Vertex v = load_vertex(q, start, ti);
+  load_vertex_direction(q, kp.rough_thr, start, ti, v);
   loaded(v);
   float rgb[3];
   const uint8_t hit = lookup_key(tv, dtype, vertex_key(kp, q, v), rgb);
@@ -288,7 +290,9 @@ __global__ void __launch_bounds__(256) k_query_hier(QryPtrs q, uint64_t n, uint3
                                                     uint8_t* level_out) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
+  const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
+  Vertex v = load_vertex(q, start, ti);
+  load_vertex_direction(q, kp.rough_thr, start, ti, v);
   loaded(v);
   // the bins once, the position at each level
   int ok = (int)finite3(v.p[0], v.p[1], v.p[2]) & (int)finite3(v.n[0], v.n[1], v.n[2]);
@@ -328,11 +332,12 @@ __global__ void __launch_bounds__(kEstThreads) k_estimate(EstPtrs a, uint64_t n,
   const uint32_t last = n - start < kEstThreads ? (uint32_t)(n - start) - 1 : kEstThreads - 1;
   const uint32_t t = threadIdx.x < last ? threadIdx.x : last;
   const bool hr = a.qo.rough != nullptr, hf = a.qo.footprint != nullptr;
-  const Vertex v = load_vertex(a.qo, kp_o.rough_thr, start, t);
-  float wi[3] = {0.0f, 0.0f, 0.0f};
-  if (hr) load_direction(a.qi.ox, a.qi.oy, a.qi.oz, start, t, v.rough, kp_i.rough_thr, wi);
+  Vertex v = load_vertex(a.qo, start, t);
   const float g[3] = {ld_once_at(a.gr + start, t), ld_once_at(a.gg + start, t), ld_once_at(a.gb + start, t)};
   const float w = ld_once_at(a.wp + start, t);
+  float wi[3] = {0.0f, 0.0f, 0.0f};
+  if (hr) load_direction(a.qi.ox, a.qi.oy, a.qi.oz, start, t, v.rough, kp_i.rough_thr, wi);
+  load_vertex_direction(a.qo, kp_o.rough_thr, start, t, v);
   loaded(v);
   asm volatile("" : : "v"(wi[0]), "v"(wi[1]), "v"(wi[2]));
   // the two keys share the position and normal where the tables share their
@@ -388,7 +393,7 @@ __global__ void __launch_bounds__(256) k_step_samples(StepPtrs a, uint64_t n, Ke
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
   const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
-  const Vertex v = load_vertex(a.next, kp.rough_thr, start, ti);
+  Vertex v = load_vertex(a.next, start, ti);
   const bool le = a.le_r != nullptr;
   float e[3] = {0.0f, 0.0f, 0.0f};
   if (le) {
@@ -397,6 +402,7 @@ __global__ void __launch_bounds__(256) k_step_samples(StepPtrs a, uint64_t n, Ke
     e[2] = ld_once_at(a.le_b + start, ti);
   }
   const float t[3] = {ld_once_at(a.t_r + start, ti), ld_once_at(a.t_g + start, ti), ld_once_at(a.t_b + start, ti)};
+  load_vertex_direction(a.next, kp.rough_thr, start, ti, v);
   loaded(v);
   float L[3];
   lookup_key(tv, dtype, vertex_key(kp, a.next, v), L);
@@ -816,7 +822,9 @@ __global__ void __launch_bounds__(256) k_query_sh(QryPtrs q, uint64_t n, KeyPara
                                                   uint8_t* found) {
   const uint64_t start = (uint64_t)xcd_order(blockIdx.x, gridDim.x) * 256;
   const uint32_t last = n - start < 256 ? (uint32_t)(n - start) - 1 : 255u;
-  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
+  const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
+  Vertex v = load_vertex(q, start, ti);
+  load_vertex_direction(q, kp.rough_thr, start, ti, v);
   loaded(v);
   const uint64_t key = vertex_key(kp, q, v);
   float rgb[3] = {0.0f, 0.0f, 0.0f};

@@ -1391,7 +1391,9 @@ __global__ void __launch_bounds__(kQueryBlock) k_query_batch(const BatchSession*
   const TableView tv = S.tv;
   const KeyParams kp = S.kp;
   const QryPtrs q = S.q;
-  const Vertex v = load_vertex(q, kp.rough_thr, start, threadIdx.x < last ? threadIdx.x : last);
+  const uint32_t ti = threadIdx.x < last ? threadIdx.x : last;
+  Vertex v = load_vertex(q, start, ti);
+  load_vertex_direction(q, kp.rough_thr, start, ti, v);
   loaded(v);
   float rgb[3];
   const uint8_t hit = lookup_key(tv, S.bp.dtype, vertex_key(kp, q, v), rgb);
