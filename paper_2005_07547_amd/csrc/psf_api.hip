@@ -1035,7 +1035,7 @@ PSF_API psf_status psf_iterate_batch(psf_batch* b, const psf_session* sessions, 
   for (uint32_t i : batch) {
     const psf_table* t = sessions[i].table;
     records += sessions[i].n;
-    if (psf::dense_launch(sessions[i].n, t->tv)) dense_records += sessions[i].n;
+    if (psf::dense_session(sessions[i].n, t->tv)) dense_records += sessions[i].n;
     most_parts = std::max(most_parts, 1u << (t->cfg.log2_slots - t->tv.part_log2));
     given = given || t->cfg.bin_per != 0;
   }
@@ -1043,9 +1043,7 @@ PSF_API psf_status psf_iterate_batch(psf_batch* b, const psf_session* sessions, 
   // Dense sessions take a merge launch of their own, behind the others'; where
   // they hold most of the records, the others join theirs (eight sessions of 1
   // to 2 records a slot: 405 us in two launches, 377 in one, and in rounds for
-  // all 437; in partitions of 2^12 slots 399, 400 and 412; with the variance
-  // 162, 152 and 179; sixteen of 1 to 4 with 2 to 4 samples a pixel: 5.01 ms,
-  // 5.02 and 4.96).
+  // all 437; with the variance 162, 152 and 179).
   const bool all_dense = dense_records > records / 2;
   uint32_t tiles = 0, parts = 0, qblks = 0, trans = 0;
   for (uint32_t j = 0; j < batch.size(); ++j) {
@@ -1067,7 +1065,7 @@ PSF_API psf_status psf_iterate_batch(psf_batch* b, const psf_session* sessions, 
     if (!d.fused_query) d.pv.perm = nullptr;
     d.pv.weights = d.rec.weight != nullptr;
     d.pv.tile = tile;
-    d.pv.dense = all_dense ? psf::dense_fits(t->tv) : psf::dense_launch(ss.n, t->tv);
+    d.pv.dense = all_dense ? psf::dense_fits(t->tv) : psf::dense_session(ss.n, t->tv);
     d.tile_begin = tiles;
     d.ntiles = (uint32_t)((ss.n + tile - 1) / tile);
     d.part_begin = parts;

@@ -157,6 +157,7 @@ uint32_t small_tiles(uint64_t cap, uint32_t nparts);
 // or (the default) the touched ones in rounds; and whether its records are
 // that many, whatever its partitions.
 bool dense_launch(uint64_t n, const TableView& tv);
+bool dense_session(uint64_t n, const TableView& tv);  // the same in a batch
 bool dense_fits(const TableView& tv);  // whether those sums fit a block
 bool dense_records(uint64_t n, uint64_t slots);
 uint32_t update_grid(uint64_t nslots);  // blocks of the streaming update

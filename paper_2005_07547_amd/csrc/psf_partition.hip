@@ -167,8 +167,8 @@ __device__ __forceinline__ uint32_t run_head(unsigned long long cont, uint32_t l
 // where records carry more; 8192: 1024 with 8).  The pass waits on one dependent
 // step after another (record loads, LDS ranks, scan, staging), so twice the
 // wavefronts with half the records each hide more of it: 70.6 -> 62.0 us for
-// 3,686,400 records (900 tiles) against 512 threads with 8, 174 -> 163 us for
-// 1688 tiles of 6144.  Compiled for the wavefronts per SIMD of two blocks a CU
+// 3,686,400 records (900 tiles) against 512 threads with 8 (58.5 since), 174 ->
+// 163 us for 1688 tiles of 6144 (155 since).  Compiled for the wavefronts per SIMD of two blocks a CU
 // (one of 8192 records, by its LDS; twelve weighted records a thread spill at
 // 128 registers and run one block a CU at 137).
 constexpr int bin_waves(uint32_t threads, uint32_t per, bool weights) {
@@ -525,8 +525,8 @@ __global__ void __launch_bounds__(kTransposeThreads) k_transpose_runs(PartView p
 // round, in half the LDS that sums for every slot would take: a CU holds 24
 // wavefronts (two blocks of 4096 slots, four of 2048, eight of 1024) instead
 // of 16, in separate blocks that are not all in the same phase.  3,686,400
-// records into 2^22 slots: 98 -> 82 us; 10,368,000 into 2^24: 336 -> 278 us
-// (266 with the answers of its 16-bit state staged in half the bytes).
+// records into 2^22 slots: 98 -> 82 us (75 since); 10,368,000 into 2^24: 336 ->
+// 278 us (266 with the answers of its 16-bit state staged in half the bytes).
 // (32 wavefronts need 64 registers and spill 37 more: 176 us.)  A partition
 // with more touched cells takes further rounds over its entries, each of them
 // as long as the first; dense_launch tells the launches that would.
@@ -1149,6 +1149,16 @@ bool dense_fits(const TableView& tv) {
 
 bool dense_launch(uint64_t n, const TableView& tv) {
   return dense_records(n, 1ull << tv.log2_slots) && dense_fits(tv);
+}
+
+// In a batch, whose other sessions' blocks fill the CUs meanwhile, rounds in
+// partitions of 2^12 slots hold out to 5/2 records a slot: sixteen sessions of
+// 0.75 to 4 with 1 to 4 samples a pixel 4.99 ms, from 5/4 on 5.05, in rounds for
+// all 4.96; eight of 1 to 2 with one sample a pixel 413 us, 401 and 412; eight of
+// 2 to 4 592 us, 592 and 1165.
+bool dense_session(uint64_t n, const TableView& tv) {
+  const uint64_t slots = 1ull << tv.log2_slots;
+  return dense_launch(n, tv) && (tv.part_log2 < 12 || n > slots * 2 + slots / 2);
 }
 
 static bool tile_ok(uint32_t tile) {

@@ -95,8 +95,8 @@ def test_dense_and_ordinary_sessions_share_a_batch():
     from paper_2005_07547_amd import psf
     kinds = [("plain", 12, 4000), ("variance", 11, 40003), ("plain", 8, 10241), ("weighted", 10, 9000),
              ("weighted", 11, 12289), ("variance", 10, 500), ("plain", 12, 30000)]
-    few = [("plain", 12, 10241), ("weighted", 10, 10240), ("variance", 11, 9000), ("variance", 8, 12000),
-           ("plain", 8, 8000), ("plain", 11, 10000)]
+    few = [("plain", 12, 20481), ("weighted", 10, 10240), ("variance", 11, 9000), ("variance", 8, 12000),
+           ("plain", 8, 8000), ("plain", 11, 10000), ("plain", 12, 20480)]
     # mostly dense records, mostly others (two merge launches), dense ones alone
     for some in (kinds, few, kinds[1:3] + kinds[4:5], kinds[6:]):
         tabs = [_table(psf, k, p, max_batch=50000) for k, p, _ in some]
